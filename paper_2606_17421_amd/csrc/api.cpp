@@ -293,6 +293,9 @@ int ckks_ctx_create(ckks_ctx** out, uint32_t log_n, uint32_t num_limbs, const ui
   const size_t o_qrec = blob.add(qrec.data(), L * 8);
   const size_t o_bar = blob.add(bar.data(), L * 4);
   const size_t o_p256 = blob.add(p256.data(), p256.size() * 4);
+  std::vector<uint32_t> rns(size_t(L) * ckks::kRnsConstWords);
+  ckks::rns_consts(c->q.data(), L, rns.data());
+  const size_t o_rns = blob.add(rns.data(), rns.size() * 4);
   size_t o_perm = 0, o_pos = 0, o_fft = 0, o_rfft = 0, o_dct = 0;
   {  // encode tables (every supported N)
     const uint32_t M = n / 2, P = n / 4;
@@ -371,6 +374,7 @@ int ckks_ctx_create(ckks_ctx** out, uint32_t log_n, uint32_t num_limbs, const ui
   t.q_recip = reinterpret_cast<const double*>(base + o_qrec);
   t.barrett = reinterpret_cast<const uint32_t*>(base + o_bar);
   t.pow256 = reinterpret_cast<const uint32_t*>(base + o_p256);
+  t.rns = reinterpret_cast<const uint32_t*>(base + o_rns);
   {
     t.slot_perm = reinterpret_cast<const uint32_t*>(base + o_perm);
     t.slot_pos = reinterpret_cast<const uint32_t*>(base + o_pos);

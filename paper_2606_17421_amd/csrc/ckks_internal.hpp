@@ -15,6 +15,9 @@ constexpr int kMaxLogN = 16;
 constexpr uint32_t kMaxMacDin = 1u << 24;  // largest d_in of the scalar MAC entry point
 constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;  // per-GPU workspace of the no-allocation MAC
 constexpr int kMaxDevices = 64;
+constexpr int kRnsChannels = 8;      // small moduli of the residue-channel MAC
+constexpr int kRnsConstWords = 12;   // its per-limb constants
+constexpr uint32_t kRnsTaken = 0x524e5301u;  // decision word: the residue-channel kernels compute the call
 
 // Per-context device tables.  All arrays live in one device allocation owned
 // by the context; [L][N] arrays are limb-major.
@@ -35,6 +38,7 @@ struct Tables {
   const double* q_recip;       // [L]     1.0 / q_l rounded to nearest
   const uint32_t* barrett;     // [L]     floor(2^61 / q_l) (< 2^32 for q_l > 2^29)
   const uint32_t* pow256;      // [L][8]  256^s mod q_l, s < 8
+  const uint32_t* rns;         // [L][kRnsConstWords] residue-channel MAC
   // Encode tables (M = N/2, P = N/4).
   const uint32_t* slot_perm;   // [M]  slot index j whose odd exponent is 2u+1 (up to sign)
   const uint32_t* slot_pos;    // [M]  index m of slot j in the Makhoul-ordered real sequence
@@ -138,6 +142,15 @@ bool mac_mfma_supported(uint32_t d_in);
 hipError_t launch_mac_scalar_mfma(const Tables& t, const uint32_t* w_enc, const uint32_t* ct_in,
                                   uint32_t* ct_out, uint32_t d_out, uint32_t d_in, uint32_t limbs,
                                   void* workspace, hipStream_t s);
+
+// Residue-channel MAC (mac_rns.hip): its per-limb constants [L][kRnsConstWords]
+// and the launch, which launches nothing when the shape or the workspace does
+// not suit it.  The launched kernels set *decision (device) to kRnsTaken when
+// the weights qualify and the output is theirs, else to 0.
+void rns_consts(const uint32_t* q, uint32_t L, uint32_t* out);
+hipError_t launch_mac_scalar_rns(const Tables& t, const uint32_t* w_enc, const uint32_t* ct_in, uint32_t* ct_out,
+                                 uint32_t d_out, uint32_t d_in, uint32_t limbs, void* workspace,
+                                 size_t workspace_bytes, uint32_t* decision, hipStream_t s, bool* launched);
 
 hipError_t launch_mac_poly(const Tables& t, const uint32_t* pt, const uint32_t* ct_in,
                            uint32_t* ct_out, uint32_t d_out, uint32_t d_in, uint32_t limbs,

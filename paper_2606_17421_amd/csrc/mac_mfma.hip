@@ -32,7 +32,8 @@
 //    issued two steps ahead) into an LDS double buffer and synchronises, two
 //    workgroups per CU; XCD-aware grouped order keeps a row group's weights
 //    and the columns its row tiles share in one XCD's L2.
-// In both, rows past d_in read as zero through the buffer range check, and a
+// Large layers whose weights need the fourth digit go through residue channels
+// instead (mac_rns.hip).  In both forms rows past d_in read as zero through the buffer range check, and a
 // wave-uniform branch per tile selects three or four weight digits.
 #include <mutex>
 
@@ -99,10 +100,16 @@ __device__ __forceinline__ void to_fragments(const uint32_t (&x)[16], v4i (&f)[4
 // are consecutive and each XCD runs a contiguous range of them, so a tile's
 // rows come from HBM once into that XCD's L2 (with the limb as the slow grid
 // dimension every line was fetched about once per limb).
+// kGuard: end at once when *done says that the residue-channel kernels took the
+// call.
+template <bool kGuard>
 __global__ __launch_bounds__(kThreads) void mfma_prep_kernel(
     const uint32_t* __restrict__ qtab, const uint32_t* __restrict__ w_enc, uint32_t d_out,
     uint32_t d_in, uint32_t limbs, uint32_t mt_total, uint32_t ks_total, v4i* __restrict__ adig,
-    uint32_t* __restrict__ flags) {
+    uint32_t* flags, const uint32_t* done) {
+  if constexpr (kGuard) {
+    if (*done == kRnsTaken) return;
+  }
   const uint32_t G = gridDim.x;
   uint32_t lid = blockIdx.x;
   if ((G & 7u) == 0) lid = (lid & 7u) * (G >> 3) + (lid >> 3);
@@ -395,11 +402,15 @@ __device__ __forceinline__ void cs_tile(const Tables& tb, const v4i* __restrict_
   epilogue<NDA>(acc, tb, l, lane, out, row_bytes);
 }
 
+template <bool kGuard>  // as mfma_prep_kernel's
 __global__ __launch_bounds__(kCsThreads, 1) void mac_cs_kernel(
     Tables tb, const v4i* __restrict__ adig, const uint32_t* __restrict__ flags,
     const uint32_t* __restrict__ ct_in, uint32_t* __restrict__ ct_out, uint32_t d_out, uint32_t d_in,
-    uint32_t limbs, uint32_t mt_total, uint32_t ks_total, uint32_t tiles_n) {
+    uint32_t limbs, uint32_t mt_total, uint32_t ks_total, uint32_t tiles_n, const uint32_t* done) {
   __shared__ v4i bs[kCsMaxKs][kFragsPerStep];  // residue digit fragments of every k-step (128 KiB)
+  if constexpr (kGuard) {
+    if (*done == kRnsTaken) return;
+  }
   // Consecutive workgroup ids alternate XCDs: each XCD takes a contiguous range
   // of (limb, column tile), so the workgroups resident on one XCD share a limb's
   // weight fragments in its L2.
@@ -520,15 +531,28 @@ hipError_t launch_mac_scalar_mfma(const Tables& t, const uint32_t* w_enc, const 
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   v4i* adig = reinterpret_cast<v4i*>(ws);
   uint32_t* flags = reinterpret_cast<uint32_t*>(ws + s.adig_bytes);
-  mfma_prep_kernel<<<dim3(s.mt_total * limbs), kThreads, 0, st>>>(t.q, w_enc, d_out, d_in, limbs, s.mt_total,
-                                                                  s.ks_total, adig, flags);
   const size_t grid = static_cast<size_t>(limbs) * s.tiles_n * s.tiles_m;
+  const size_t cgrid = static_cast<size_t>(limbs) * s.tiles_n;
   if (grid >= (size_t(1) << 31)) return hipErrorInvalidValue;  // tile indices are 32-bit
+  // The residue-channel kernels where they apply, in the space of the digit
+  // fragments.  Whether the weights qualify is known on the device only, so the
+  // digit-split kernels follow, and end at once when the decision word, the
+  // first tile flag, says that the output is there (a flag is 0 or 1, so
+  // writing it changes no other workgroup's mind).
+  bool tried = false;
   if (d_in <= kCsMaxDin) {
-    const size_t cgrid = static_cast<size_t>(limbs) * s.tiles_n;
-    if (cgrid >= (size_t(1) << 31)) return hipErrorInvalidValue;
-    mac_cs_kernel<<<static_cast<uint32_t>(cgrid), kCsThreads, 0, st>>>(t, adig, flags, ct_in, ct_out, d_out, d_in,
-                                                                      limbs, s.mt_total, s.ks_total, s.tiles_n);
+    const hipError_t e = launch_mac_scalar_rns(t, w_enc, ct_in, ct_out, d_out, d_in, limbs, ws, s.adig_bytes, flags, st,
+                                               &tried);
+    if (e != hipSuccess) return e;
+  }
+  const uint32_t* done = tried ? flags : nullptr;
+  const auto prep = tried ? mfma_prep_kernel<true> : mfma_prep_kernel<false>;
+  prep<<<dim3(s.mt_total * limbs), kThreads, 0, st>>>(t.q, w_enc, d_out, d_in, limbs, s.mt_total, s.ks_total, adig, flags,
+                                                      done);
+  if (d_in <= kCsMaxDin) {
+    const auto mac = tried ? mac_cs_kernel<true> : mac_cs_kernel<false>;
+    mac<<<static_cast<uint32_t>(cgrid), kCsThreads, 0, st>>>(t, adig, flags, ct_in, ct_out, d_out, d_in, limbs,
+                                                            s.mt_total, s.ks_total, s.tiles_n, done);
     return hipGetLastError();
   }
   mac_mfma_kernel<<<static_cast<uint32_t>(grid), kThreads, 0, st>>>(t, adig, flags, ct_in, ct_out, d_out, d_in, limbs,
