@@ -11,34 +11,23 @@
 // coefficients lie within q0 q1 / 2 in magnitude) and encrypted afresh under
 // limbs_out limbs.
 //
-// Encryption and decryption run the batched NTT kernels over the c0 rows (or
-// the output rows) through their row-group stride, with pointwise passes
-// around them, 16 bytes per thread and limb.  The refresh, up to N = 2^15, is
-// two transform kernels (decrypt + inverse, lift + forward + combine), or up to
-// 2^13 for decode-size counts one fused kernel split by output limb; at 2^16
-// (a row exceeds the LDS) it is the pass structure of encryption and decryption.
+// Encryption and decryption, up to N = 2^15, are one kernel each: the error's
+// residues (or c0 + c1 (.) s) are formed as the transform loads its row and the
+// combine (or the coefficients) leave with its stores, 256 workgroups and more
+// running as the batched transforms do.  At 2^16 (a row exceeds the LDS) the same
+// work rides on the first and last passes of the staged transforms.  100
+// features at 2^16 and 8 limbs, encoded, encrypted and decrypted: 1065 -> 815 us
+// (separate error, transform and pointwise passes before; the encoding, 400 us,
+// is the same in both).  The refresh, up to N = 2^15, is two transform kernels
+// (decrypt + inverse, lift + forward + combine), or up to 2^13 for decode-size
+// counts one fused kernel split by output limb; at 2^16 the staged passes of
+// decryption and encryption with the lift in the column pass's loads.
+#include <type_traits>
+
 #include "ntt_core.hpp"
 
 namespace ckks {
 namespace {
-
-constexpr int kThreads = 256;
-
-// 16-byte accesses use native vector types: written with the HIP uint4
-// struct, the read-modify-write loop of the encrypt combine compiled to an
-// empty kernel.
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-typedef int32_t v4s __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ v4u ld4(const uint32_t* p) { return *reinterpret_cast<const v4u*>(p); }
-__device__ __forceinline__ v4s ld4(const int32_t* p) { return *reinterpret_cast<const v4s*>(p); }
-__device__ __forceinline__ void st4(uint32_t* p, v4u v) { *reinterpret_cast<v4u*>(p) = v; }
-
-// Signed 64-bit x mod q, in [0, q).
-__device__ __forceinline__ uint32_t reduce_i64(int64_t x, uint32_t q, double qr) {
-  const uint64_t ax = static_cast<uint64_t>(x < 0 ? -x : x);
-  const uint32_t r = reduce_u64(ax, q, qr);
-  return (x < 0 && r != 0) ? q - r : r;
-}
 
 // floor(w 2^32 / q) for w < q (the Shoup companion of w): the fp64 estimate is
 // within one of it, and one remainder check fixes it.
@@ -81,124 +70,6 @@ __device__ __forceinline__ uint32_t lift_residue(const LiftConst& c, uint32_t x0
 // registers; per-lane offsets and per-element constants index into it).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, uint32_t n) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, n * 4, 0x00020000);
-}
-
-// Thread -> (ciphertext c, coefficient quad k4) over count * N/4 quads.
-struct Quad {
-  size_t c;
-  uint32_t k;
-  bool ok;
-};
-__device__ __forceinline__ Quad quad_of(uint32_t n, uint32_t count) {
-  const size_t i = static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x;
-  const uint32_t per = n >> 2;
-  Quad r;
-  r.c = i / per;
-  r.k = static_cast<uint32_t>(i % per) * 4;
-  r.ok = r.c < count;
-  return r;
-}
-
-// ct[c][0][l][k] = e[c][k] mod q_l for every limb (coefficient form).
-__global__ __launch_bounds__(kThreads) void err_rows_kernel(Tables tb, const int32_t* __restrict__ e,
-                                                            uint32_t count, uint32_t limbs,
-                                                            uint32_t* __restrict__ ct) {
-  const uint32_t n = tb.n;
-  const Quad p = quad_of(n, count);
-  if (!p.ok) return;
-  const v4s ev = ld4(e + p.c * n + p.k);
-  for (uint32_t l = 0; l < limbs; ++l) {
-    const uint32_t q = tb.q[l];
-    v4u r;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) r[j] = ev[j] < 0 ? q - static_cast<uint32_t>(-ev[j]) : static_cast<uint32_t>(ev[j]);
-    st4(ct + ((p.c * 2) * limbs + l) * n + p.k, r);
-  }
-}
-
-// c0 <- c0 + pt - a (.) s, c1 <- a  (pt == nullptr: no plaintext term).
-__global__ __launch_bounds__(kThreads) void enc_combine_kernel(Tables tb, const uint32_t* __restrict__ pt,
-                                                               const uint32_t* __restrict__ s_ntt,
-                                                               const uint32_t* __restrict__ a, uint32_t count,
-                                                               uint32_t limbs, uint32_t* __restrict__ ct) {
-  const uint32_t n = tb.n;
-  const Quad p = quad_of(n, count);
-  if (!p.ok) return;
-  for (uint32_t l = 0; l < limbs; ++l) {
-    const uint32_t q = tb.q[l], mu = tb.barrett[l];
-    const size_t row = (p.c * limbs + l) * n + p.k;
-    uint32_t* c0p = ct + ((p.c * 2) * limbs + l) * n + p.k;
-    uint32_t* c1p = c0p + static_cast<size_t>(limbs) * n;
-    const v4u c0 = ld4(c0p);
-    const v4u av = ld4(a + row);
-    const v4u sv = ld4(s_ntt + static_cast<size_t>(l) * n + p.k);
-    const v4u pv = pt ? ld4(pt + row) : v4u{0, 0, 0, 0};
-    v4u o;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = sub_mod(add_mod(c0[j], pv[j], q), mul_mod_barrett(av[j], sv[j], q, mu), q);
-    st4(c0p, o);
-    st4(c1p, av);
-  }
-}
-
-// out row (c * out_gstride + out_off + l) <- c0 + c1 (.) s of ciphertext c,
-// limb l < limbs_used, read from ct[count][2][ct_limbs][N] (NTT form).
-__global__ __launch_bounds__(kThreads) void dec_pointwise_kernel(Tables tb, const uint32_t* __restrict__ ct,
-                                                                 uint32_t ct_limbs, const uint32_t* __restrict__ s_ntt,
-                                                                 uint32_t count, uint32_t limbs_used,
-                                                                 uint32_t* __restrict__ out, uint32_t out_gstride,
-                                                                 uint32_t out_off) {
-  const uint32_t n = tb.n;
-  const Quad p = quad_of(n, count);
-  if (!p.ok) return;
-  for (uint32_t l = 0; l < limbs_used; ++l) {
-    const uint32_t q = tb.q[l], mu = tb.barrett[l];
-    const uint32_t* c0p = ct + ((p.c * 2) * ct_limbs + l) * n + p.k;
-    const v4u c0 = ld4(c0p);
-    const v4u c1 = ld4(c0p + static_cast<size_t>(ct_limbs) * n);
-    const v4u sv = ld4(s_ntt + static_cast<size_t>(l) * n + p.k);
-    v4u o;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = add_mod(c0[j], mul_mod_barrett(c1[j], sv[j], q, mu), q);
-    st4(out + (p.c * out_gstride + out_off + l) * n + p.k, o);
-  }
-}
-
-// Refresh lift.  dec rows (c * 2 limbs_out + limbs_out + {0, 1}) hold the
-// decrypted coefficient residues mod q0, q1.  x = r0 + q0 ((r1 - r0) q0^-1
-// mod q1) is the CRT value in [0, q0 q1); centred, plus the fresh error, it
-// is written mod q_l into the c0 rows of ct_out for l < limbs_out.
-__global__ __launch_bounds__(kThreads) void dte_lift_kernel(Tables tb, const int32_t* __restrict__ e,
-                                                            uint32_t count, uint32_t limbs_out,
-                                                            uint32_t* __restrict__ ct_out) {
-  const uint32_t n = tb.n;
-  const Quad p = quad_of(n, count);
-  if (!p.ok) return;
-  const uint32_t q0 = tb.q[0], q1 = tb.q[1];
-  const uint32_t w = tb.qinv[0 * tb.L + 1], ws = tb.qinv_shoup[0 * tb.L + 1];  // q0^-1 mod q1
-  const uint64_t Q2 = static_cast<uint64_t>(q0) * q1;
-  const uint32_t* d0 = ct_out + ((p.c * 2) * limbs_out + limbs_out) * n + p.k;
-  const v4u r0v = ld4(d0);
-  const v4u r1v = ld4(d0 + n);
-  const v4s ev = ld4(e + p.c * n + p.k);
-  int64_t m[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const uint32_t r0 = r0v[j];
-    const uint32_t r0m = r0 >= q1 ? r0 - q1 : r0;  // r0 < q0 < 2 q1
-    const uint32_t t = mul_shoup(sub_mod(r1v[j], r0m, q1), w, ws, q1);
-    const uint64_t x = static_cast<uint64_t>(r0) + static_cast<uint64_t>(q0) * t;  // [0, q0 q1)
-    const int64_t xc = x > Q2 / 2 ? static_cast<int64_t>(x) - static_cast<int64_t>(Q2) : static_cast<int64_t>(x);
-    m[j] = xc + ev[j];
-  }
-  for (uint32_t l = 0; l < limbs_out; ++l) {
-    const uint32_t q = tb.q[l];
-    const double qr = tb.q_recip[l];
-    v4u o;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = reduce_i64(m[j], q, qr);
-    st4(ct_out + ((p.c * 2) * limbs_out + l) * n + p.k, o);
-  }
 }
 
 // Fused refresh for N <= 2^13 and at most one workgroup per CU (a decode-size
@@ -309,16 +180,16 @@ __global__ __launch_bounds__(RefreshPlan<LOGN>::P::T, RefreshPlan<LOGN>::kWavesP
 //     the value mod q_l plus the fresh error, the forward transform, and
 //     c0 = . - a (.) s written coalesced;
 // c1 = a: rows from 2 on by (2), rows 0 and 1 (the scratch) copied afterwards.
-template <int LOGN>
-__global__ __launch_bounds__((WholePlan<LOGN>::P::T), (WholePlan<LOGN>::kWavesPerSimd)) void dte_dec_intt_kernel(
+template <int LOGN, bool LAT>
+__global__ __launch_bounds__((WholePlan<LOGN, LAT>::P::T), (WholePlan<LOGN, LAT>::kWavesPerSimd)) void dec_intt_kernel(
     Tables tb, const uint32_t* __restrict__ ct_in, uint32_t limbs_in, const uint32_t* __restrict__ s_ntt,
-    uint32_t limbs_out, uint32_t* __restrict__ ct_out) {
-  using P = typename WholePlan<LOGN>::P;
-  constexpr int LOGE = WholePlan<LOGN>::LOGE;
+    uint32_t limbs_used, uint32_t* __restrict__ out, uint32_t out_gstride) {
+  using P = typename WholePlan<LOGN, LAT>::P;
+  constexpr int LOGE = WholePlan<LOGN, LAT>::LOGE;
   constexpr int N = P::B;
   __shared__ uint32_t lds[P::lds_words];
-  const size_t c = blockIdx.x >> 1;
-  const uint32_t l = blockIdx.x & 1, t = threadIdx.x;
+  const size_t c = blockIdx.x / limbs_used;
+  const uint32_t l = blockIdx.x % limbs_used, t = threadIdx.x;
   const uint32_t q = tb.q[l], mu = tb.barrett[l];
   const uint32_t vofs = pos_coalesced<LOGE>(t, 0) * 4;
   const auto r_c0 = row_rsrc(ct_in + ((c * 2) * limbs_in + l) * N, N);
@@ -337,7 +208,7 @@ __global__ __launch_bounds__((WholePlan<LOGN>::P::T), (WholePlan<LOGN>::kWavesPe
   const size_t tl = static_cast<size_t>(l) << LOGN;
   inv_block<LOGN, LOGN, LOGE>(v, t, 0, tb.inv + tl, tb.inv_shoup + tl, q, lds);
   const uint32_t ni = tb.ninv[l], nis = tb.ninv_shoup[l];
-  uint32_t* r = ct_out + ((c * 2 + 1) * limbs_out + l) * N;
+  uint32_t* r = out + (c * out_gstride + l) * N;
 #pragma unroll
   for (int j = 0; j < P::E; ++j) r[P::template pos<0>(t, j)] = mul_shoup(v[j], ni, nis, q);
 }
@@ -433,12 +304,235 @@ __global__ __launch_bounds__((WholePlan<LOGN>::P::T), (WholePlan<LOGN>::kWavesPe
   }
 }
 
+// e mod q for |e| < q.
+__device__ __forceinline__ uint32_t small_residue(int32_t e, uint32_t q) {
+  return e < 0 ? static_cast<uint32_t>(e) + q : static_cast<uint32_t>(e);
+}
+
+// Elements of one row in the coalesced layout, as buffer loads in batches of kB,
+// each batch issued before the previous one is used (x[0], x[1] alternate).
+constexpr int kB = 8;
+struct RowAt {
+  __amdgpu_buffer_rsrc_t r;
+  uint32_t ofs;
+  __device__ __forceinline__ uint32_t load(int j) const { return __builtin_amdgcn_raw_buffer_load_b32(r, ofs, j << 8, 0); }
+  __device__ __forceinline__ void store(uint32_t x, int j) const { __builtin_amdgcn_raw_buffer_store_b32(x, r, ofs, j << 8, 0); }
+};
+
+// c0 = v + pt - a (.) s and c1 = a for the elements j < E of one row (pt absent
+// without kPt); every position 64 j + ofs / 4 of the row.
+template <int E, bool kPt>
+__device__ __forceinline__ void combine_row(const uint32_t (&v)[E], const RowAt& pt, const RowAt& a, const RowAt& s,
+                                            const RowAt& c0, const RowAt& c1, uint32_t q, uint32_t mu) {
+  constexpr int B = kB < E ? kB : E;
+  uint32_t ya[2][B], ys[2][B], yp[2][B];
+  auto load = [&](int set, int j0) {
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      ya[set][i] = a.load(j0 + i);
+      ys[set][i] = s.load(j0 + i);
+      if constexpr (kPt) yp[set][i] = pt.load(j0 + i);
+    }
+  };
+  load(0, 0);
+#pragma unroll
+  for (int j0 = 0; j0 < E; j0 += B) {
+    const int cur = (j0 / B) & 1;
+    if (j0 + B < E) load(cur ^ 1, j0 + B);
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      uint32_t x = v[j0 + i];
+      if constexpr (kPt) x = add_mod(x, yp[cur][i], q);
+      c0.store(sub_mod(x, mul_mod_barrett(ya[cur][i], ys[cur][i], q, mu), q), j0 + i);
+      c1.store(ya[cur][i], j0 + i);
+    }
+  }
+}
+
+// Encryption for N <= 2^15: one workgroup per (ciphertext, limb) row takes the
+// error's residues through the forward transform and combines on the way out:
+// 5 row transfers (e from L2 for all limbs but one) where error rows, a batched
+// transform and a pointwise pass took 8.  The limbs of a ciphertext run
+// together on one XCD and read its error row from HBM once.
+template <int LOGN, bool LAT, bool kPt>
+__global__ __launch_bounds__((WholePlan<LOGN, LAT>::P::T), (WholePlan<LOGN, LAT>::kWavesPerSimd)) void encrypt_kernel(
+    Tables tb, const uint32_t* __restrict__ pt, const uint32_t* __restrict__ s_ntt, const uint32_t* __restrict__ a,
+    const int32_t* __restrict__ e, uint32_t limbs, uint32_t* __restrict__ ct) {
+  using P = typename WholePlan<LOGN, LAT>::P;
+  constexpr int LOGE = WholePlan<LOGN, LAT>::LOGE;
+  constexpr int N = P::B;
+  __shared__ uint32_t lds[P::lds_words];
+  const uint32_t G = gridDim.x;
+  uint32_t lid = blockIdx.x;
+  if ((G & 7u) == 0) lid = (lid & 7u) * (G >> 3) + (lid >> 3);
+  const size_t c = lid / limbs;
+  const uint32_t l = lid % limbs, t = threadIdx.x;
+  const uint32_t q = tb.q[l], mu = tb.barrett[l];
+  const auto er = row_rsrc(e + c * N, N);
+  uint32_t v[P::E];
+#pragma unroll
+  for (int j = 0; j < P::E; ++j)
+    v[j] = small_residue(static_cast<int32_t>(__builtin_amdgcn_raw_buffer_load_b32(er, t * 4, P::template pos<0>(0, j) * 4, 0)), q);
+  const size_t tl = static_cast<size_t>(l) << LOGN;
+  fwd_block<LOGN, LOGN, LOGE>(v, t, 0, tb.fwd + tl, tb.fwd_shoup + tl, q, lds);
+  wave_relayout<LOGN, LOGE, false>(v, t, lds);
+  __builtin_amdgcn_sched_barrier(0);  // the combine's loads stay after the transform
+  const uint32_t vofs = pos_coalesced<LOGE>(t, 0) * 4;
+  const size_t row = (c * limbs + l) * N;
+  combine_row<P::E, kPt>(v, {row_rsrc(kPt ? pt + row : nullptr, N), vofs}, {row_rsrc(a + row, N), vofs},
+                         {row_rsrc(s_ntt + tl, N), vofs}, {row_rsrc(ct + ((c * 2) * limbs + l) * N, N), vofs},
+                         {row_rsrc(ct + ((c * 2 + 1) * limbs + l) * N, N), vofs}, q, mu);
+}
+
+// ---- N = 2^16 (a row exceeds the LDS): the transforms' column and block passes
+// of the batched kernels with the pointwise work folded into their first loads
+// and last stores.  A column pass over the error (or the lifted refresh value)
+// forms each limb's residues as it loads; a block pass combines as it stores.
+// Decryption's block pass forms c0 + c1 (.) s as it loads.  6 row transfers per
+// limb for an encryption (10 with separate passes), 5 for a decryption (7).
+constexpr int kColLogE = 6;
+constexpr int kColThreads = 256;
+constexpr int kColBlocks = (1 << (16 - kColLogE)) / kColThreads;
+constexpr int kBlkLogB = 10;
+constexpr int kBlkLogE = 4;
+constexpr int kBlocksPerRow = 1 << (16 - kBlkLogB);
+
+// Column pass of row (c, l): kLift false, v = e mod q_l; kLift true, the CRT value
+// of the two rows at `dec` (residues mod q0, q1) plus e, mod q_l.  Written to row
+// c * gstride + l of `out`, in the lazy range.  The limbs of one ciphertext are
+// numbered together on one XCD and share the rows they read.
+template <bool kLift>
+__global__ __launch_bounds__(kColThreads, 2) void rlwe16_cols_kernel(Tables tb, const int32_t* __restrict__ e,
+                                                                     const uint32_t* dec, uint32_t limbs,
+                                                                     uint32_t gstride, uint32_t* out) {
+  using P = Plan<16, kColLogE>;
+  const uint32_t G = gridDim.x;
+  uint32_t lid = blockIdx.x;
+  if ((G & 7u) == 0) lid = (lid & 7u) * (G >> 3) + (lid >> 3);
+  const uint32_t l = lid % limbs, cb = (lid / limbs) % kColBlocks;
+  const size_t c = lid / limbs / kColBlocks;
+  const uint32_t col = cb * kColThreads + threadIdx.x;
+  const uint32_t q = tb.q[l];
+  const int32_t* ec = e + (c << 16) + col;
+  uint32_t v[P::E];
+  if constexpr (kLift) {
+    const uint32_t* d0 = dec + ((c * gstride) << 16) + col;
+    const uint32_t q0 = tb.q[0], q1 = tb.q[1];
+    const uint32_t w = tb.qinv[0 * tb.L + 1], ws = tb.qinv_shoup[0 * tb.L + 1];  // q0^-1 mod q1
+    const uint64_t half = static_cast<uint64_t>(q0) * q1 / 2;
+    const LiftConst lc = lift_const(q0, q1, q, tb.q_recip[l]);
+#pragma unroll
+    for (int j = 0; j < P::E; ++j) {
+      const uint32_t o = P::template pos<0>(0, j);
+      const uint32_t x0 = d0[o], r0m = x0 >= q1 ? x0 - q1 : x0;
+      const uint32_t k = mul_shoup(sub_mod(d0[65536 + o], r0m, q1), w, ws, q1);
+      const bool neg = static_cast<uint64_t>(x0) + static_cast<uint64_t>(q0) * k > half;
+      v[j] = lift_residue(lc, x0, k, neg, ec[o]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < P::E; ++j) v[j] = small_residue(ec[P::template pos<0>(0, j)], q);
+  }
+  const size_t tl = static_cast<size_t>(l) << 16;
+  fwd_group<16, 16, kColLogE, 0>(v, col, 0, tb.fwd + tl, tb.fwd_shoup + tl, q);  // [0, 4q)
+  uint32_t* o = out + ((c * gstride + l) << 16) + col;
+#pragma unroll
+  for (int j = 0; j < P::E; ++j) __builtin_nontemporal_store(v[j], &o[P::template pos<0>(0, j)]);
+}
+
+// Block pass of the c0 rows of ct [count][2][limbs][N], in place, with the combine.
+template <bool kPt>
+__global__ __launch_bounds__(1 << (kBlkLogB - kBlkLogE)) void rlwe16_blocks_combine_kernel(
+    Tables tb, const uint32_t* __restrict__ pt, const uint32_t* __restrict__ s_ntt, const uint32_t* __restrict__ a,
+    uint32_t limbs, uint32_t* ct) {
+  using P = Plan<kBlkLogB, kBlkLogE>;
+  __shared__ uint32_t lds[P::lds_words];
+  const size_t r = blockIdx.x / kBlocksPerRow;
+  const uint32_t blk = blockIdx.x % kBlocksPerRow, t = threadIdx.x;
+  const size_t c = r / limbs;
+  const uint32_t l = static_cast<uint32_t>(r % limbs);
+  const uint32_t q = tb.q[l], mu = tb.barrett[l];
+  const size_t boff = static_cast<size_t>(blk) << kBlkLogB;
+  uint32_t* c0 = ct + (((c * 2) * limbs + l) << 16) + boff;
+  uint32_t v[P::E];
+#pragma unroll
+  for (int j = 0; j < P::E; ++j) v[j] = __builtin_nontemporal_load(&c0[P::template pos<0>(t, j)]);
+  const size_t tl = static_cast<size_t>(l) << 16;
+  fwd_block<16, kBlkLogB, kBlkLogE>(v, t, blk, tb.fwd + tl, tb.fwd_shoup + tl, q, lds);
+  wave_relayout<kBlkLogB, kBlkLogE, false>(v, t, lds);
+  const size_t row = (r << 16) + boff;
+  const uint32_t n = P::B;
+  combine_row<P::E, kPt>(v, {row_rsrc(kPt ? pt + row : nullptr, n), t * 4}, {row_rsrc(a + row, n), t * 4},
+                         {row_rsrc(s_ntt + tl + boff, n), t * 4}, {row_rsrc(c0, n), t * 4},
+                         {row_rsrc(c0 + (static_cast<size_t>(limbs) << 16), n), t * 4}, q, mu);
+}
+
+// Inverse block pass of c0 + c1 (.) s, limbs l < limbs_used of ct [count][2][ct_limbs][N],
+// into row c * out_gstride + l of `out` (the column pass follows).
+__global__ __launch_bounds__(1 << (kBlkLogB - kBlkLogE)) void dec16_blocks_kernel(
+    Tables tb, const uint32_t* __restrict__ ct, uint32_t ct_limbs, const uint32_t* __restrict__ s_ntt,
+    uint32_t limbs_used, uint32_t* __restrict__ out, uint32_t out_gstride) {
+  using P = Plan<kBlkLogB, kBlkLogE>;
+  __shared__ uint32_t lds[P::lds_words];
+  const size_t r = blockIdx.x / kBlocksPerRow;
+  const uint32_t blk = blockIdx.x % kBlocksPerRow, t = threadIdx.x;
+  const size_t c = r / limbs_used;
+  const uint32_t l = static_cast<uint32_t>(r % limbs_used);
+  const uint32_t q = tb.q[l], mu = tb.barrett[l];
+  const size_t boff = static_cast<size_t>(blk) << kBlkLogB, tl = static_cast<size_t>(l) << 16;
+  const uint32_t* c0 = ct + (((c * 2) * ct_limbs + l) << 16) + boff + t;
+  const uint32_t* c1 = c0 + (static_cast<size_t>(ct_limbs) << 16);
+  const uint32_t* sp = s_ntt + tl + boff + t;
+  uint32_t v[P::E], x1[P::E], xs[P::E];
+#pragma unroll
+  for (int j = 0; j < P::E; ++j) {
+    v[j] = __builtin_nontemporal_load(&c0[64 * j]);
+    x1[j] = __builtin_nontemporal_load(&c1[64 * j]);
+    xs[j] = sp[64 * j];
+  }
+#pragma unroll
+  for (int j = 0; j < P::E; ++j) v[j] = add_mod(v[j], mul_mod_barrett(x1[j], xs[j], q, mu), q);
+  wave_relayout<kBlkLogB, kBlkLogE, true>(v, t, lds);
+  inv_block<16, kBlkLogB, kBlkLogE>(v, t, blk, tb.inv + tl, tb.inv_shoup + tl, q, lds);
+  uint32_t* o = out + ((c * out_gstride + l) << 16) + boff;
+#pragma unroll
+  for (int j = 0; j < P::E; ++j) __builtin_nontemporal_store(v[j], &o[P::template pos<0>(t, j)]);
+}
+
+// Fewer rows than CUs take the latency plan (2^13 and 2^14), as the batched transforms.
+template <int LOGN>
+hipError_t launch_encrypt_whole(const Tables& t, const uint32_t* pt, const uint32_t* s_ntt, const uint32_t* a,
+                                const int32_t* e, uint32_t count, uint32_t limbs, uint32_t* ct, hipStream_t s) {
+  const uint32_t rows = count * limbs;
+  auto go = [&](auto lat) {
+    constexpr bool kLat = decltype(lat)::value;
+    constexpr uint32_t T = WholePlan<LOGN, kLat>::P::T;
+    if (pt) encrypt_kernel<LOGN, kLat, true><<<rows, T, 0, s>>>(t, pt, s_ntt, a, e, limbs, ct);
+    else encrypt_kernel<LOGN, kLat, false><<<rows, T, 0, s>>>(t, pt, s_ntt, a, e, limbs, ct);
+  };
+  if ((LOGN == 13 || LOGN == 14) && rows < t.num_cus) go(std::true_type{});
+  else go(std::false_type{});
+  return hipGetLastError();
+}
+
+template <int LOGN>
+hipError_t launch_decrypt_whole(const Tables& t, const uint32_t* ct, const uint32_t* s_ntt, uint32_t count,
+                                uint32_t limbs, uint32_t* m, hipStream_t s) {
+  const uint32_t rows = count * limbs;
+  if ((LOGN == 13 || LOGN == 14) && rows < t.num_cus)
+    dec_intt_kernel<LOGN, true><<<rows, WholePlan<LOGN, true>::P::T, 0, s>>>(t, ct, limbs, s_ntt, limbs, m, limbs);
+  else
+    dec_intt_kernel<LOGN, false><<<rows, WholePlan<LOGN>::P::T, 0, s>>>(t, ct, limbs, s_ntt, limbs, m, limbs);
+  return hipGetLastError();
+}
+
 template <int LOGN>
 hipError_t launch_refresh_two(const Tables& t, const uint32_t* ct_in, uint32_t limbs_in, const uint32_t* s_ntt,
                               const uint32_t* a, const int32_t* e, uint32_t count, uint32_t limbs_out,
                               uint32_t* ct_out, hipStream_t s) {
   constexpr uint32_t T = WholePlan<LOGN>::P::T;
-  dte_dec_intt_kernel<LOGN><<<dim3(2 * count), T, 0, s>>>(t, ct_in, limbs_in, s_ntt, limbs_out, ct_out);
+  dec_intt_kernel<LOGN, false><<<dim3(2 * count), T, 0, s>>>(
+      t, ct_in, limbs_in, s_ntt, 2, ct_out + static_cast<size_t>(limbs_out) * t.n, 2 * limbs_out);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   dte_lift_ntt_kernel<LOGN><<<dim3(count * limbs_out), T, 0, s>>>(t, e, s_ntt, a, limbs_out, ct_out);
@@ -458,31 +552,40 @@ hipError_t launch_refresh_fused(const Tables& t, const uint32_t* ct_in, uint32_t
   return hipGetLastError();
 }
 
-uint32_t quad_grid(uint32_t n, uint32_t count) {
-  const size_t quads = static_cast<size_t>(count) * (n / 4);
-  return static_cast<uint32_t>((quads + kThreads - 1) / kThreads);
-}
-
 }  // namespace
 
 hipError_t launch_encrypt(const Tables& t, const uint32_t* pt, const uint32_t* s_ntt, const uint32_t* a,
                           const int32_t* e, uint32_t count, uint32_t limbs, uint32_t* ct, hipStream_t s) {
-  const uint32_t grid = quad_grid(t.n, count);
-  err_rows_kernel<<<grid, kThreads, 0, s>>>(t, e, count, limbs, ct);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  err = launch_ntt(t, ct, static_cast<size_t>(count) * limbs, limbs, false, s, 2 * limbs);  // c0 rows
-  if (err != hipSuccess) return err;
-  enc_combine_kernel<<<grid, kThreads, 0, s>>>(t, pt, s_ntt, a, count, limbs, ct);
+  switch (t.log_n) {
+    case 10: return launch_encrypt_whole<10>(t, pt, s_ntt, a, e, count, limbs, ct, s);
+    case 11: return launch_encrypt_whole<11>(t, pt, s_ntt, a, e, count, limbs, ct, s);
+    case 12: return launch_encrypt_whole<12>(t, pt, s_ntt, a, e, count, limbs, ct, s);
+    case 13: return launch_encrypt_whole<13>(t, pt, s_ntt, a, e, count, limbs, ct, s);
+    case 14: return launch_encrypt_whole<14>(t, pt, s_ntt, a, e, count, limbs, ct, s);
+    case 15: return launch_encrypt_whole<15>(t, pt, s_ntt, a, e, count, limbs, ct, s);
+    default: break;
+  }
+  const uint32_t rows = count * limbs;
+  rlwe16_cols_kernel<false><<<rows * kColBlocks, kColThreads, 0, s>>>(t, e, nullptr, limbs, 2 * limbs, ct);
+  const auto blocks = pt ? rlwe16_blocks_combine_kernel<true> : rlwe16_blocks_combine_kernel<false>;
+  blocks<<<rows * kBlocksPerRow, 1 << (kBlkLogB - kBlkLogE), 0, s>>>(t, pt, s_ntt, a, limbs, ct);
   return hipGetLastError();
 }
 
 hipError_t launch_decrypt(const Tables& t, const uint32_t* ct, const uint32_t* s_ntt, uint32_t count,
                           uint32_t limbs, uint32_t* m, hipStream_t s) {
-  dec_pointwise_kernel<<<quad_grid(t.n, count), kThreads, 0, s>>>(t, ct, limbs, s_ntt, count, limbs, m, limbs, 0);
-  const hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  return launch_ntt(t, m, static_cast<size_t>(count) * limbs, limbs, true, s);
+  switch (t.log_n) {
+    case 10: return launch_decrypt_whole<10>(t, ct, s_ntt, count, limbs, m, s);
+    case 11: return launch_decrypt_whole<11>(t, ct, s_ntt, count, limbs, m, s);
+    case 12: return launch_decrypt_whole<12>(t, ct, s_ntt, count, limbs, m, s);
+    case 13: return launch_decrypt_whole<13>(t, ct, s_ntt, count, limbs, m, s);
+    case 14: return launch_decrypt_whole<14>(t, ct, s_ntt, count, limbs, m, s);
+    case 15: return launch_decrypt_whole<15>(t, ct, s_ntt, count, limbs, m, s);
+    default: break;
+  }
+  dec16_blocks_kernel<<<count * limbs * kBlocksPerRow, 1 << (kBlkLogB - kBlkLogE), 0, s>>>(t, ct, limbs, s_ntt, limbs, m,
+                                                                                          limbs);
+  return launch_intt16_cols(t, m, static_cast<size_t>(count) * limbs, limbs, limbs, s);
 }
 
 hipError_t launch_refresh(const Tables& t, const uint32_t* ct_in, uint32_t limbs_in, const uint32_t* s_ntt,
@@ -514,24 +617,19 @@ hipError_t launch_refresh(const Tables& t, const uint32_t* ct_in, uint32_t limbs
     case 13: return launch_refresh_fused<13>(t, ct_in, limbs_in, s_ntt, a, e, count, limbs_out, ct_out, s);
     default: break;
   }
-  // N = 2^16 (a row exceeds the LDS): pointwise passes around the batched
-  // transforms
-  const uint32_t grid = quad_grid(t.n, count);
+  // N = 2^16: limbs 0 and 1 of c0 + c1 (.) s, inverse-transformed, in the c1 rows
+  // 0 and 1 of ct_out (scratch); the lift's column pass into the c0 rows; its
+  // block pass with the combine, which writes every c1 row.
   const uint32_t gs = 2 * limbs_out;
-  // 1. limbs 0 and 1 of c0 + c1 (.) s into the c1 rows 0, 1 of ct_out (scratch), then INTT them
-  dec_pointwise_kernel<<<grid, kThreads, 0, s>>>(t, ct_in, limbs_in, s_ntt, count, 2, ct_out, gs, limbs_out);
-  hipError_t err = hipGetLastError();
+  uint32_t* dec = ct_out + static_cast<size_t>(limbs_out) * t.n;
+  dec16_blocks_kernel<<<count * 2 * kBlocksPerRow, 1 << (kBlkLogB - kBlkLogE), 0, s>>>(t, ct_in, limbs_in, s_ntt, 2, dec,
+                                                                                      gs);
+  const hipError_t err = launch_intt16_cols(t, dec, static_cast<size_t>(count) * 2, 2, gs, s);
   if (err != hipSuccess) return err;
-  err = launch_ntt(t, ct_out + static_cast<size_t>(limbs_out) * t.n, static_cast<size_t>(count) * 2, 2, true, s, gs);
-  if (err != hipSuccess) return err;
-  // 2. CRT lift + fresh error, reduced under limbs_out limbs, into the c0 rows; NTT them
-  dte_lift_kernel<<<grid, kThreads, 0, s>>>(t, e, count, limbs_out, ct_out);
-  err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  err = launch_ntt(t, ct_out, static_cast<size_t>(count) * limbs_out, limbs_out, false, s, gs);
-  if (err != hipSuccess) return err;
-  // 3. c0 -= a (.) s, c1 = a (overwrites the scratch rows)
-  enc_combine_kernel<<<grid, kThreads, 0, s>>>(t, nullptr, s_ntt, a, count, limbs_out, ct_out);
+  const uint32_t rows = count * limbs_out;
+  rlwe16_cols_kernel<true><<<rows * kColBlocks, kColThreads, 0, s>>>(t, e, dec, limbs_out, gs, ct_out);
+  rlwe16_blocks_combine_kernel<false><<<rows * kBlocksPerRow, 1 << (kBlkLogB - kBlkLogE), 0, s>>>(t, nullptr, s_ntt, a,
+                                                                                                 limbs_out, ct_out);
   return hipGetLastError();
 }
 

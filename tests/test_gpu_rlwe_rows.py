@@ -1,0 +1,37 @@
+"""Encryption and decryption at the edges of their dispatch: below and at one row per CU
+(the two plans of 2^13 and 2^14 rows), one limb, the largest whole-row ring, and the
+staged 2^16 form, each with and without a plaintext, against the oracle bit for bit."""
+import numpy as np
+import pytest
+
+from oracle import rlwe as OR
+from test_gpu_rlwe import setup, residues_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("log_n,limbs,count", [(13, 5, 51), (13, 4, 64), (14, 3, 85), (14, 4, 65), (15, 2, 3), (12, 1, 9), (16, 1, 3)])
+@pytest.mark.parametrize("with_pt", [True, False])
+def test_rows_match_the_oracle(gpu_lib, log_n, limbs, count, with_pt):
+    ck = gpu_lib
+    ctx, qs, psis, n, st, s, s_ntt, m, e, a = setup(ck, log_n, limbs, count, 900 + log_n + limbs)
+    if not with_pt:
+        m = np.zeros_like(m)
+    # the extremes of the error range of every limb, |e| < q_l
+    e[0, :4] = [min(qs) - 1, 1 - min(qs), 0, -1]
+    pt = None
+    if with_pt:
+        pt = ck.to_device(residues_of(m, qs))
+        ck.ckks_ntt(ctx, pt, count, limbs)
+    ct = ck.empty_u32((count, 2, limbs, n))
+    ct.fill_(-1)
+    ck.ckks_encrypt(ctx, pt, s_ntt, ck.to_device(a), ck.to_device(e), count, limbs, ct)
+    pick = sorted({0, count // 2, count - 1})
+    got = ck.to_host_u32(ct)[pick]
+    want = OR.encrypt(m[pick], s, a[pick], e[pick], qs, psis, log_n).astype(np.uint32)
+    assert np.array_equal(got, want)
+    out = ck.empty_u32((count, limbs, n))
+    out.fill_(-1)
+    ck.ckks_decrypt(ctx, ct, s_ntt, count, limbs, out)
+    # an encryption of m with error e decrypts to m + e in every limb
+    assert np.array_equal(ck.to_host_u32(out), residues_of(m + e, qs))
