@@ -64,31 +64,29 @@ __global__ __launch_bounds__(kThreads) void mac_scalar_valu_kernel(
 // consecutive row groups are adjacent in logical order, and each XCD runs a
 // contiguous range of logical ids, so the shared ciphertext columns are
 // fetched once into that XCD's L2.  Four rows per thread when the grid
-// still holds at least 8 workgroups per CU; narrower layers (the 32-output
-// groups of a decode stack or a BSGS giant-step set) take two rows per thread
-// for twice the workgroups: 47.7 -> 32.2 us at 32 x 32, 4 limbs, N = 2^13
-// (2.8 -> 4.2 TB/s of plaintext stream).  Per input the row loads are all
-// issued before the first product (a ragged last group re-reads row 0 for its
-// missing rows and discards those sums), so a wave waits on memory once per
-// input instead of once per row: 31.1 -> 24.9 us at 32 x 32, 2^13, 4 limbs.
-// The 4-row kernel (wide layers) loads the plaintexts, which are read once,
-// non-temporally, so that they do not displace the ciphertext columns every
-// row group re-reads from L2: 669 -> 623 us at 64 x 64, 2^15, 6 limbs.  At
-// 32 x 32 the non-temporal loads were slower, so the 2-row kernel keeps plain
-// loads.  Both kernels store their outputs non-temporally (written once): 621
-// -> 600 us at 64 x 64, 2^15, 6 limbs; 53 -> 49.5 us at 32 x 32, 2^14, 4 limbs.
+// still holds at least 2 workgroups per CU; narrower layers (a 32-output BSGS
+// giant-step set at 2^13) take two rows per thread for twice the workgroups.
+// A 16-group decode stack of 32 x 32, 4 limbs, N = 2^14, whose weights come from
+// HBM on every call: 2327 us with two rows, 2262 us with four.  Per input the
+// row loads are all issued before the first product (a ragged last group
+// re-reads row 0 for its missing rows and discards those sums), so a wave waits
+// on memory once per input instead of once per row: 31.1 -> 24.9 us at 32 x 32,
+// 2^13, 4 limbs (the next input's loads issued ahead of the products as well
+// gave nothing).  The plaintexts are read once and loaded non-temporally, so
+// that they displace neither the ciphertext columns that every row group
+// re-reads from L2 nor the last-level cache: 669 -> 623 us at 64 x 64, 2^15,
+// 6 limbs, 2397 -> 2327 us for the decode stack, 145 -> 140 us for a 1024 x 1024
+// BSGS product whose 134 MB of diagonals alternate with another's (only a loop
+// over the same diagonals, resident in the last-level cache, is slower with
+// them).  Outputs are stored non-temporally (written once): 621 -> 600 us at
+// 64 x 64, 2^15, 6 limbs; 53 -> 49.5 us at 32 x 32, 2^14, 4 limbs.
 constexpr int kPolySlots = 4;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-template <bool kNonTemporal>
 __device__ __forceinline__ uint4 load_pt(const uint4* p) {
-  if constexpr (kNonTemporal) {
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-  } else {
-    return *p;
-  }
+  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 template <int kPolyRows>
@@ -131,7 +129,7 @@ __global__ __launch_bounds__(kThreads) void mac_poly_kernel(
 #pragma unroll
       for (int r = 0; r < kPolyRows; ++r) {
         const uint32_t rr = r < rows ? r : 0;  // rows >= 1; sums of rows past d_out are not stored
-        pv[r] = load_pt<kPolyRows == 4>(&p_ptr[rr * p_row + static_cast<size_t>(i) * ln4]);
+        pv[r] = load_pt(&p_ptr[rr * p_row + static_cast<size_t>(i) * ln4]);
       }
       const uint32_t xs0[4] = {x0.x, x0.y, x0.z, x0.w}, xs1[4] = {x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
@@ -185,7 +183,7 @@ hipError_t launch_mac_poly(const Tables& t, const uint32_t* pt, const uint32_t* 
                            hipStream_t s) {
   const size_t blocks = static_cast<size_t>(limbs) * (t.n / (kThreads * kPolySlots));
   const size_t grid4 = static_cast<size_t>((d_out + 3) / 4) * blocks;
-  if (grid4 >= 8 * static_cast<size_t>(t.num_cus)) {
+  if (grid4 >= 2 * static_cast<size_t>(t.num_cus)) {
     mac_poly_kernel<4><<<static_cast<uint32_t>(grid4), kThreads, 0, s>>>(t, pt, ct_in, ct_out, d_out, d_in, limbs);
   } else {
     const size_t grid2 = static_cast<size_t>((d_out + 1) / 2) * blocks;
