@@ -1,0 +1,52 @@
+"""Edges of size rules: the smallest and odd row counts of the 2^15 inverse transform whose
+workgroups walk the rows, and the poly MAC on both sides of its rows-per-thread rule."""
+import numpy as np
+import pytest
+
+from oracle import linear as OL
+from oracle import ntt as ON
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("limbs,count", [(1, 1023), (1, 1024), (1, 1301), (3, 342), (2, 513)])
+def test_intt_walk_n15(gpu_lib, limbs, count):
+    import torch
+    ck = gpu_lib
+    ctx = ck.Context(15, limbs)
+    n, qs = ctx.n, ctx.moduli
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(count)
+    x = torch.empty((count, limbs, n), dtype=torch.int32, device="cuda:0")
+    for l, q in enumerate(qs):
+        x[:, l] = torch.randint(0, q, (count, n), dtype=torch.int32, device="cuda:0", generator=g)
+    y = x.clone()
+    ck.ckks_intt(ctx, y, count, limbs)
+    for c in sorted({0, 255 // limbs, 256 // limbs, count - 1}):
+        for l in range(limbs):
+            want = ON.intt(ck.to_host_u32(x[c, l]), qs[l], ctx.roots[l], 15)
+            assert np.array_equal(ck.to_host_u32(y[c, l]), want.astype(np.uint32))
+    ck.ckks_ntt(ctx, y, count, limbs)
+    assert torch.equal(x, y)
+    ctx.close()
+
+
+@pytest.mark.parametrize("d_out", [27, 28, 29, 30, 32, 33])
+def test_mac_poly_rows_per_thread(gpu_lib, d_out):
+    """N = 2^14, 4 limbs: 29 outputs are the fewest that take four rows a thread."""
+    ck = gpu_lib
+    log_n, limbs, d_in = 14, 4, 17
+    ctx = ck.Context(log_n, limbs)
+    qs, n = ctx.moduli, ctx.n
+    rng = np.random.default_rng(d_out)
+    pt = gen.uniform_residues(rng, (d_out, d_in), qs, n)
+    ct = gen.uniform_residues(rng, (d_in, 2), qs, n)
+    pt[:, :, :, 0] = (np.array(qs, dtype=np.uint32) - 1)        # the largest sums
+    ct[:, :, :, 0] = (np.array(qs, dtype=np.uint32) - 1)
+    out = ck.empty_u32((d_out, 2, limbs, n))
+    out.fill_(-1)
+    ck.ckks_linear_mac_poly(ctx, ck.to_device(pt), ck.to_device(ct), out, d_out, d_in, limbs)
+    rows = sorted({0, 1, d_out // 2, d_out - 3, d_out - 2, d_out - 1})
+    assert np.array_equal(ck.to_host_u32(out)[rows], OL.mac_poly(pt, ct, qs, rows=rows).astype(np.uint32))
+    ctx.close()
