@@ -85,11 +85,17 @@ __device__ __forceinline__ void fft_pass(double2* a, int s, const double2* __res
 // in one workgroup per slot vector, with the whole-polynomial transform's
 // thread count.  The spectral buffer (P double2, padded) and the transform's exchange
 // buffer share the LDS.  When every rounded coefficient fits in int32 (the
-// CKKS-scaled weights of the workloads) each thread keeps its 2P/T of them in
-// registers; per limb it writes the residues of their four mirrored positions
-// into the exchange buffer and the transform starts from there (group-0
-// layout).  Otherwise the workgroup writes every limb's coefficient residues
-// to its output rows first and transforms the rows in place from there.
+// CKKS-scaled weights of the workloads) each thread keeps them, 2P/T of its own
+// and from 2^13 up the mirrored ones of another thread too, as the elements of
+// the transform's group-0 layout; a limb then starts from registers, three
+// operations an element ahead of its butterflies.  (Residues reduced to [0, q)
+// and scattered through the LDS for every limb before: 2.28 -> 2.02 ms for 4096
+// vectors of 2^15 x 6 limbs, 216 -> 202 us for 1024 of 2^14 x 4, 195 -> 175 us
+// for 2048 of 2^13 x 4.)  Otherwise the workgroup forms the coefficients again
+// from the spectrum, one at a time, writes every limb's residues to its output
+// rows and transforms the rows in place: kept in registers for this case, the
+// coefficients cost the common one its spills.  (Such vectors: 302 -> 260 us
+// for 1024 of 2^14 x 4 limbs, 58-65 -> 60-68 us for 2^12.)
 template <int LOGN>
 struct FusedPlan {
   using W = WholePlan<LOGN>;
@@ -101,14 +107,11 @@ struct FusedPlan {
   static constexpr int LDS_WORDS = (SPEC_WORDS > NP::lds_words) ? SPEC_WORDS : NP::lds_words;
 };
 
-// Slots -> spectrum -> rounded coefficients p(k), p(k + P) for the thread's k
-// (k = t + T i), as exact doubles.  Ends with every thread done reading LDS.
+// Slots -> spectrum, left in the LDS.
 template <int LOGN>
-__device__ __forceinline__ bool encode_spectrum(const Tables& tb, const double* __restrict__ z, double scale,
-                                                double2* a, double (&p_lo)[FusedPlan<LOGN>::KPT],
-                                                double (&p_hi)[FusedPlan<LOGN>::KPT]) {
+__device__ __forceinline__ void encode_spectrum(const Tables& tb, const double* __restrict__ z, double2* a) {
   using FP = FusedPlan<LOGN>;
-  constexpr int M = FP::M, P = FP::P, T = FP::T, N = FP::N;
+  constexpr int M = FP::M, P = FP::P, T = FP::T;
   // Stage the slot vector in LDS with coalesced 16-byte loads, then gather
   // the Makhoul-ordered pairs from there (the spectrum reuses the same LDS).
   {
@@ -139,29 +142,30 @@ __device__ __forceinline__ bool encode_spectrum(const Tables& tb, const double* 
   for (; s + 3 <= FP::LOGP; s += 3) fft_pass<FP::LOGP, 3>(a, s, tb.fft_tw, T);
   if (FP::LOGP - s == 2) fft_pass<FP::LOGP, 2>(a, s, tb.fft_tw, T);
   if (FP::LOGP - s == 1) fft_pass<FP::LOGP, 1>(a, s, tb.fft_tw, T);
-  const double two_over_n = 2.0 / N;
-  bool fits = true;
-#pragma unroll
-  for (int i = 0; i < FP::KPT; ++i) {
-    const int k = threadIdx.x + T * i;
-    const int kr = static_cast<int>(__brev(static_cast<uint32_t>(k)) >> (32 - FP::LOGP));
-    const int km = (P - k) & (P - 1);
-    const int kmr = static_cast<int>(__brev(static_cast<uint32_t>(km)) >> (32 - FP::LOGP));
-    const double2 ck = a[spec_pad(kr)];
-    const double2 cm = a[spec_pad(kmr)];
-    const double2 cmc = make_double2(cm.x, -cm.y);
-    const double2 e = make_double2(0.5 * (ck.x + cmc.x), 0.5 * (ck.y + cmc.y));
-    const double2 dd = csub(ck, cmc);
-    const double2 o = make_double2(0.5 * dd.y, -0.5 * dd.x);
-    const double2 wo = cmul(tb.rfft_tw[k], o);
-    const double2 v_lo = cadd(e, wo);
-    const double2 v_hi = csub(e, wo);
-    const double2 t_lo = tb.dct_tw[k], t_hi = tb.dct_tw[k + P];
-    p_lo[i] = rint(scale * (two_over_n * (t_lo.x * v_lo.x - t_lo.y * v_lo.y)));
-    p_hi[i] = rint(scale * (two_over_n * (t_hi.x * v_hi.x - t_hi.y * v_hi.y)));
-    fits = fits && fabs(p_lo[i]) < 2147483648.0 && fabs(p_hi[i]) < 2147483648.0;
-  }
-  return __syncthreads_and(fits);
+}
+
+// Rounded coefficients p(k) and p(k + P) from the spectrum, as exact doubles.
+template <int LOGN>
+__device__ __forceinline__ void fold_spectrum(const Tables& tb, const double2* a, double scale, int k, double& p_lo,
+                                              double& p_hi) {
+  using FP = FusedPlan<LOGN>;
+  constexpr int P = FP::P;
+  constexpr double two_over_n = 2.0 / FP::N;
+  const int kr = static_cast<int>(__brev(static_cast<uint32_t>(k)) >> (32 - FP::LOGP));
+  const int km = (P - k) & (P - 1);
+  const int kmr = static_cast<int>(__brev(static_cast<uint32_t>(km)) >> (32 - FP::LOGP));
+  const double2 ck = a[spec_pad(kr)];
+  const double2 cm = a[spec_pad(kmr)];
+  const double2 cmc = make_double2(cm.x, -cm.y);
+  const double2 e = make_double2(0.5 * (ck.x + cmc.x), 0.5 * (ck.y + cmc.y));
+  const double2 dd = csub(ck, cmc);
+  const double2 o = make_double2(0.5 * dd.y, -0.5 * dd.x);
+  const double2 wo = cmul(tb.rfft_tw[k], o);
+  const double2 v_lo = cadd(e, wo);
+  const double2 v_hi = csub(e, wo);
+  const double2 t_lo = tb.dct_tw[k], t_hi = tb.dct_tw[k + P];
+  p_lo = rint(scale * (two_over_n * (t_lo.x * v_lo.x - t_lo.y * v_lo.y)));
+  p_hi = rint(scale * (two_over_n * (t_hi.x * v_hi.x - t_hi.y * v_hi.y)));
 }
 
 // Residues mod q of coefficients k, k + P and their mirrors at index x of
@@ -192,63 +196,79 @@ __global__ __launch_bounds__(FusedPlan<LOGN>::T, WholePlan<LOGN>::kWavesPerSimd)
   uint32_t* out = pt + b * static_cast<size_t>(limbs) * N;
   const uint32_t t = threadIdx.x;
 
-  double p_lo[FP::KPT], p_hi[FP::KPT];
-  const bool all_fit = encode_spectrum<LOGN>(tb, z, scale, reinterpret_cast<double2*>(lds), p_lo, p_hi);
-  if (all_fit) {  // workgroup-uniform
-    int32_t c_lo[FP::KPT], c_hi[FP::KPT];
+  double2* spec = reinterpret_cast<double2*>(lds);
+  encode_spectrum<LOGN>(tb, z, spec);
+  constexpr bool kKeep = LOGN >= 13;
+  int32_t c[NP::E];
+  bool fits = true;
 #pragma unroll
-    for (int i = 0; i < FP::KPT; ++i) {
-      c_lo[i] = static_cast<int32_t>(p_lo[i]);
-      c_hi[i] = static_cast<int32_t>(p_hi[i]);
+  for (int i = 0; i < FP::KPT; ++i) {
+    double lo, hi;
+    fold_spectrum<LOGN>(tb, spec, scale, static_cast<int>(t) + T * i, lo, hi);
+    const bool ok = fmax(fabs(lo), fabs(hi)) < 2147483648.0;
+    fits = fits && ok;
+    c[i] = ok ? static_cast<int32_t>(lo) : 0;
+    c[FP::KPT + i] = ok ? static_cast<int32_t>(hi) : 0;
+  }
+  const bool all_fit = __syncthreads_and(fits);  // every thread is done reading the spectrum for now
+  if (all_fit) {  // workgroup-uniform
+    // The thread's outputs k = t + T i and k + P are its elements j = i and
+    // KPT + i of the transform's group-0 layout; the mirrored half of the
+    // polynomial (m_{N-k} = -m_k, m_{N/2} = 0) comes through the LDS, from 2^13 up
+    // once, to stay in registers beside the row of every limb.  Below it goes
+    // through per limb, as residues: the few waves wait little for each other,
+    // and fewer registers are the better deal (16.9 against 18.7 us for 500
+    // vectors of 2^11, 3 limbs; 77 vectors of 2^12: 16.6 us with the half kept).
+    constexpr int E = NP::E, H = E / 2;
+    static_assert(H == 2 * FP::KPT, "spectral outputs of a thread: the lower half of its elements");
+    int32_t* own = reinterpret_cast<int32_t*>(lds) + t;                      // element j at index t + T j
+    int32_t* mir = reinterpret_cast<int32_t*>(lds) + (N - t) - T * (E - 1);  // its mirror N - t - T j
+    if constexpr (kKeep) {
+#pragma unroll
+      for (int j = 0; j < H; ++j) own[T * j] = c[j];
+      if (t == 0) own[T * H] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int j = H; j < E; ++j) c[j] = -mir[T * (E - 1 - j)];
+      __syncthreads();
     }
-    // Natural (unpadded) order for the scatter: lane t touches index t + const
-    // or N - t - const, distinct banks either way.  Index N - k for k = 0 is
-    // index N, a spare word past the row; index N/2 is written 0 separately.
-    uint32_t* b0 = lds + t;                                   // k = t + T i
-    uint32_t* b1 = lds + t + FP::P;                           // k + P
-    uint32_t* b2 = lds + (N - t) - T * (FP::KPT - 1);         // N - k      at offset T (KPT-1-i)
-    uint32_t* b3 = lds + (N - FP::P - t) - T * (FP::KPT - 1); // N - k - P  at offset T (KPT-1-i)
     for (uint32_t l = 0; l < limbs; ++l) {
       const uint32_t q = tb.q[l];
-      // x mod q for x < 2^32 by a Shoup product with w = 1: ws = floor(2^32 / q)
-      uint32_t ws = static_cast<uint32_t>(4294967296.0 * tb.q_recip[l]);
-      if (static_cast<uint64_t>(ws) * q > 0xFFFFFFFFull) --ws;
-      if (static_cast<uint64_t>(ws + 1) * q <= 0xFFFFFFFFull) ++ws;
-      uint32_t b31 = 0x80000000u - 2 * q;  // 2^31 mod q (2 q < 2^31 < 4 q)
-      b31 = min(b31, b31 - q);
-      auto residue = [&](int32_t c) {  // c mod q for |c| < 2^31
-        return sub_mod(mul_shoup(static_cast<uint32_t>(c) + 0x80000000u, 1u, ws, q), b31, q);
-      };
-      if (l > 0) __syncthreads();  // the previous transform is done with the LDS
+      // x mod q in the range [0, 4q) that the transform takes: |x| < 2^31 < 4q < 2^32
+      auto lazy = [&](int32_t x) { return static_cast<uint32_t>(x) + (static_cast<uint32_t>(x >> 31) & (4 * q)); };
+      uint32_t v[E];
+      if constexpr (kKeep) {
 #pragma unroll
-      for (int i = 0; i < FP::KPT; ++i) {
-        const uint32_t r_lo = residue(c_lo[i]), r_hi = residue(c_hi[i]);
-        b0[T * i] = r_lo;
-        b1[T * i] = r_hi;
-        b2[T * (FP::KPT - 1 - i)] = r_lo ? q - r_lo : 0;
-        b3[T * (FP::KPT - 1 - i)] = r_hi ? q - r_hi : 0;
+        for (int j = 0; j < E; ++j) v[j] = lazy(c[j]);
+      } else {
+        if (l > 0) __syncthreads();  // the previous transform is done with the LDS
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          v[j] = lazy(c[j]);
+          mir[T * (E - 1 - j)] = static_cast<int32_t>(lazy(-c[j]));  // index N for element 0 of thread 0: a spare word
+        }
+        if (t == 0) own[T * H] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = H; j < E; ++j) v[j] = static_cast<uint32_t>(own[T * j]);
       }
-      if (t == 0) lds[FP::M] = 0;  // m_{N/2} = 0
-      __syncthreads();
-      uint32_t v[NP::E];
-#pragma unroll
-      for (int j = 0; j < NP::E; ++j) v[j] = lds[NP::template pos<0>(t, j)];
       const size_t tl = static_cast<size_t>(l) << LOGN;
       fwd_block<LOGN, LOGN, LOGE>(v, t, 0, tb.fwd + tl, tb.fwd_shoup + tl, q, lds);
       wave_relayout<LOGN, LOGE, false>(v, t, lds);  // last-group layout -> wave-coalesced
-      uint32_t* row = out + static_cast<size_t>(l) * N;
+      uint32_t* row = out + static_cast<size_t>(l) * N + pos_coalesced<LOGE>(t, 0);
 #pragma unroll
-      for (int j = 0; j < NP::E; ++j) __builtin_nontemporal_store(v[j], &row[pos_coalesced<LOGE>(t, j)]);
+      for (int j = 0; j < E; ++j) __builtin_nontemporal_store(v[j], &row[j << 6]);
     }
   } else {
-    for (uint32_t l = 0; l < limbs; ++l) {
-      const uint32_t q = tb.q[l];
-      const double qr = tb.q_recip[l];
-      uint32_t* row = out + static_cast<size_t>(l) * N;
-#pragma unroll
-      for (int i = 0; i < FP::KPT; ++i)
-        scatter_residues<LOGN>([&](int x) -> uint32_t& { return row[x]; }, static_cast<int>(t) + T * i, p_lo[i],
-                               p_hi[i], q, qr);
+#pragma unroll 1
+    for (int i = 0; i < FP::KPT; ++i) {
+      double lo, hi;
+      fold_spectrum<LOGN>(tb, spec, scale, static_cast<int>(t) + T * i, lo, hi);
+      for (uint32_t l = 0; l < limbs; ++l) {
+        uint32_t* row = out + static_cast<size_t>(l) * N;
+        scatter_residues<LOGN>([&](int x) -> uint32_t& { return row[x]; }, static_cast<int>(t) + T * i, lo, hi, tb.q[l],
+                               tb.q_recip[l]);
+      }
     }
     for (uint32_t l = 0; l < limbs; ++l) {
       __syncthreads();  // coefficient rows written; the previous transform is done with the LDS

@@ -1,8 +1,10 @@
 """Edges of size rules: the smallest and odd row counts of the 2^15 inverse transform whose
-workgroups walk the rows, and the poly MAC on both sides of its rows-per-thread rule."""
+workgroups walk the rows, the poly MAC on both sides of its rows-per-thread rule, and the
+encoder with coefficients on both sides of 2^31."""
 import numpy as np
 import pytest
 
+from oracle import encode as OE
 from oracle import linear as OL
 from oracle import ntt as ON
 from workloads import gen
@@ -49,4 +51,38 @@ def test_mac_poly_rows_per_thread(gpu_lib, d_out):
     ck.ckks_linear_mac_poly(ctx, ck.to_device(pt), ck.to_device(ct), out, d_out, d_in, limbs)
     rows = sorted({0, 1, d_out // 2, d_out - 3, d_out - 2, d_out - 1})
     assert np.array_equal(ck.to_host_u32(out)[rows], OL.mac_poly(pt, ct, qs, rows=rows).astype(np.uint32))
+    ctx.close()
+
+
+@pytest.mark.parametrize("log_n", [10, 11, 12, 13, 14])
+@pytest.mark.parametrize("top", [2.0**29, 2.0**31 - 8, 2.0**31 + 8, 2.0**33])
+def test_encode_coefficients_around_int32(gpu_lib, log_n, top):
+    """The largest coefficient of random slots put at `top`, with both signs: int32 coefficients
+    stay in registers, larger ones take the wide path.  Rounding ties aside the coefficients are
+    the oracle's in every limb.  A tie: both sides' fp64 values, sums of N/2 terms, are within
+    about sqrt(N/2) 2^-53 top of the exact one, so about N/2 * 2 sqrt(N/2) 2^-53 top of a
+    vector's coefficients may round differently, by one; each shows four times (its mirror, and
+    the vector with the other sign)."""
+    ck = gpu_lib
+    limbs = 3
+    ctx = ck.Context(log_n, limbs)
+    qs, psis, n = ctx.moduli, ctx.roots, ctx.n
+    z = gen.poly_weights(np.random.default_rng(log_n), 1, 1, n // 2)[0]
+    z = np.concatenate([z, -z, z[:, ::-1] * 1e-3])
+    m = OE.encode_coeffs(z, log_n)
+    scale = top / np.max(np.abs(m))
+    want = OE.round_coeffs(m, scale)
+    assert abs(np.max(np.abs(want)) - top) <= 1
+    ties = n / 2 * 2 * np.sqrt(n / 2) * 2.0**-53 * top
+    most = 4 * (1 + ties + 3 * np.sqrt(ties))
+    pt = ck.empty_u32((3, limbs, n))
+    pt.fill_(-1)
+    ck.ckks_linear_encode_poly(ctx, ck.to_device(np.ascontiguousarray(z)), 3, limbs, scale, pt)
+    got = ck.to_host_u32(pt)
+    for l, q in enumerate(qs):
+        assert got[:, l].max() < q
+        coef = ON.intt(got[:, l], q, psis[l], log_n).astype(np.int64)
+        diff = np.mod(coef - np.mod(want, q).astype(np.int64), q)
+        off = diff != 0
+        assert np.all((diff[off] == 1) | (diff[off] == q - 1)) and off.sum() <= most, (l, off.sum(), most)
     ctx.close()
