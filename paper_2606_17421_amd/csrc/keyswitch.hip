@@ -205,12 +205,14 @@ modup_fused_kernel(Tables tb, const uint32_t* __restrict__ ct, Seq in_seq, uint3
 //     lift it to p_j and forward-transform it into D[m][i][j] (for j == i the
 //     limb itself, copied).
 // One inverse transform per digit instead of one per (digit, prime) as in
-// modup_fused_kernel, whose workgroups then outnumber the CUs.
+// modup_fused_kernel, whose workgroups then outnumber the CUs.  The latency plan
+// (twice the waves a SIMD) is the faster at every batch: 16 vectors of 1024 at
+// 2^13 748 -> 742 us a call, one 140.7 -> 139.0 us.
 template <int LOGN>
-__global__ __launch_bounds__((WholePlan<LOGN>::P::T), (WholePlan<LOGN>::kWavesPerSimd)) void modup_intt_kernel(
+__global__ __launch_bounds__((WholePlan<LOGN, true>::P::T), (WholePlan<LOGN, true>::kWavesPerSimd)) void modup_intt_kernel(
     Tables tb, const uint32_t* __restrict__ ct, Seq in_seq, uint32_t L, uint32_t* __restrict__ T) {
-  using P = typename WholePlan<LOGN>::P;
-  constexpr int LOGE = WholePlan<LOGN>::LOGE;
+  using P = typename WholePlan<LOGN, true>::P;
+  constexpr int LOGE = WholePlan<LOGN, true>::LOGE;
   constexpr int N = P::B;
   __shared__ uint32_t lds[P::lds_words];
   const uint32_t m = blockIdx.x / L, i = blockIdx.x % L;
@@ -230,11 +232,11 @@ __global__ __launch_bounds__((WholePlan<LOGN>::P::T), (WholePlan<LOGN>::kWavesPe
 }
 
 template <int LOGN>
-__global__ __launch_bounds__((WholePlan<LOGN>::P::T), (WholePlan<LOGN>::kWavesPerSimd)) void modup_ntt_kernel(
+__global__ __launch_bounds__((WholePlan<LOGN, true>::P::T), (WholePlan<LOGN, true>::kWavesPerSimd)) void modup_ntt_kernel(
     Tables tb, const uint32_t* __restrict__ ct, Seq in_seq, const uint32_t* __restrict__ T, uint32_t L,
     uint32_t* __restrict__ D) {
-  using P = typename WholePlan<LOGN>::P;
-  constexpr int LOGE = WholePlan<LOGN>::LOGE;
+  using P = typename WholePlan<LOGN, true>::P;
+  constexpr int LOGE = WholePlan<LOGN, true>::LOGE;
   constexpr int N = P::B;
   __shared__ uint32_t lds[P::lds_words];
   const uint32_t m = blockIdx.x / L, i = blockIdx.x % L, j = blockIdx.y;
@@ -374,17 +376,45 @@ __global__ __launch_bounds__(kThreads) void rot_combine_kernel(Tables tb, const 
 //     out[k] = (sigma_g(c0_m) + u0, u1),
 // the rescale's arithmetic (the P row is the last of the L + 1) with the
 // combine as its store, so u never goes through memory.  One workgroup per
-// polynomial acc[k][p] and output limb l (blockIdx.y), latency plan, as the
-// split rescale, at every batch size: two transforms per workgroup where a
-// loop over the limbs would take 1 + L per polynomial, but no intermediate
-// rows and no second launch (measured: 4% faster for 1920 rotations at 2^10,
-// 2% slower for 3968 at 2^13).  (A loop over the limbs would also spill with
-// the permuted c0 loads in its store.)
+// polynomial acc[k][p] and output limb l (blockIdx.y).  Fewer than three
+// workgroups a CU each transform the P row themselves, in one launch; above,
+// moddown_inv_kernel transforms every P row once and leaves r in T in the
+// plan's register order (kStored).  16 vectors of 1024 at 2^13, 4 limbs: 168 us
+// for the 496 rotations in one launch, 28 + 92 us in two (the call 771 -> 748
+// us); 4 vectors at 2^14 469 -> 454 us; 2 vectors at 2^13 (496 workgroups) 177
+// us a call in one launch, 178 us in two.  Both on the latency plan, whose
+// smaller register count puts twice the waves on a SIMD.  (A loop over the
+// limbs in one workgroup would spill with the permuted c0 loads in its store.)
 template <int LOGN>
+__global__ __launch_bounds__((WholePlan<LOGN, true>::P::T), (WholePlan<LOGN, true>::kWavesPerSimd)) void moddown_inv_kernel(
+    Tables tb, const uint32_t* __restrict__ acc, uint32_t L, uint32_t* __restrict__ T) {
+  using P = typename WholePlan<LOGN, true>::P;
+  constexpr int LOGE = WholePlan<LOGN, true>::LOGE;
+  constexpr int N = P::B;
+  __shared__ uint32_t lds[P::lds_words];
+  const uint32_t t = threadIdx.x;
+  const uint32_t* src = acc + (static_cast<size_t>(blockIdx.x) * (L + 1) + L) * N + pos_coalesced<LOGE>(t, 0);
+  uint32_t v[P::E];
+#pragma unroll
+  for (int j = 0; j < P::E; ++j) v[j] = src[j << 6];
+  wave_relayout<LOGN, LOGE, true>(v, t, lds);
+  const uint32_t qt = tb.q[L];
+  const size_t ttop = static_cast<size_t>(L) << LOGN;
+  inv_block<LOGN, LOGN, LOGE>(v, t, 0, tb.inv + ttop, tb.inv_shoup + ttop, qt, lds);
+  const uint32_t ni = tb.ninv[L], nis = tb.ninv_shoup[L];
+  uint32_t* dst = T + static_cast<size_t>(blockIdx.x) * N + t;
+#pragma unroll
+  for (int j = 0; j < P::E; ++j) {
+    const uint32_t y = mul_shoup(v[j], ni, nis, qt);
+    dst[j * P::T] = y > (qt >> 1) ? y - qt : y;             // centred, two's complement
+  }
+}
+
+template <int LOGN, bool kStored>
 __global__ __launch_bounds__((WholePlan<LOGN, true>::P::T), (WholePlan<LOGN, true>::kWavesPerSimd)) void
-moddown_combine_kernel(Tables tb, const uint32_t* __restrict__ acc, const uint32_t* __restrict__ ct, Seq in_seq,
-                       uint32_t L, uint32_t rotations, RotPlan plan, uint32_t* __restrict__ out, Seq out_seq,
-                       Seq copy_seq) {
+moddown_combine_kernel(Tables tb, const uint32_t* __restrict__ acc, const uint32_t* __restrict__ T,
+                       const uint32_t* __restrict__ ct, Seq in_seq, uint32_t L, uint32_t rotations, RotPlan plan,
+                       uint32_t* __restrict__ out, Seq out_seq, Seq copy_seq) {
   using P = typename WholePlan<LOGN, true>::P;
   constexpr int LOGE = WholePlan<LOGN, true>::LOGE;
   constexpr int N = P::B;
@@ -413,19 +443,25 @@ moddown_combine_kernel(Tables tb, const uint32_t* __restrict__ acc, const uint32
   uint32_t* dst = out + seq_pos(k, out_seq) * ctw + static_cast<size_t>(p) * L * N + c_base;
 
   uint32_t v[P::E];
-  const uint32_t* stop = src + static_cast<size_t>(top) * N;
-#pragma unroll
-  for (int j = 0; j < P::E; ++j) v[j] = stop[j << 6];
-  wave_relayout<LOGN, LOGE, true>(v, t, lds);
-  const uint32_t qt = tb.q[top];
-  const size_t ttop = static_cast<size_t>(top) << LOGN;
-  inv_block<LOGN, LOGN, LOGE>(v, t, 0, tb.inv + ttop, tb.inv_shoup + ttop, qt, lds);
-  const uint32_t ni = tb.ninv[top], nis = tb.ninv_shoup[top];
   int32_t r[P::E];
+  if constexpr (kStored) {
+    const uint32_t* rs = T + static_cast<size_t>(poly) * N + t;
 #pragma unroll
-  for (int j = 0; j < P::E; ++j) {
-    const uint32_t y = mul_shoup(v[j], ni, nis, qt);
-    r[j] = y > (qt >> 1) ? static_cast<int32_t>(y) - static_cast<int32_t>(qt) : static_cast<int32_t>(y);
+    for (int j = 0; j < P::E; ++j) r[j] = static_cast<int32_t>(rs[j * P::T]);
+  } else {
+    const uint32_t* stop = src + static_cast<size_t>(top) * N;
+#pragma unroll
+    for (int j = 0; j < P::E; ++j) v[j] = stop[j << 6];
+    wave_relayout<LOGN, LOGE, true>(v, t, lds);
+    const uint32_t qt = tb.q[top];
+    const size_t ttop = static_cast<size_t>(top) << LOGN;
+    inv_block<LOGN, LOGN, LOGE>(v, t, 0, tb.inv + ttop, tb.inv_shoup + ttop, qt, lds);
+    const uint32_t ni = tb.ninv[top], nis = tb.ninv_shoup[top];
+#pragma unroll
+    for (int j = 0; j < P::E; ++j) {
+      const uint32_t y = mul_shoup(v[j], ni, nis, qt);
+      r[j] = y > (qt >> 1) ? static_cast<int32_t>(y) - static_cast<int32_t>(qt) : static_cast<int32_t>(y);
+    }
   }
 
   {
@@ -664,7 +700,8 @@ __global__ __launch_bounds__(kThreads) void bsgs_mac_tile_kernel(Tables tb, cons
 
 // Workspace of rotate(): T [inputs][L][N], D [inputs][L][L+1][N],
 // acc [rotations][2][L+1][N], tmp [rotations][2][L][N] (the separate ModDown's
-// output, 2^15 and 2^16), rescale scratch.
+// output, 2^15 and 2^16; below, the inverse-transformed P rows of many
+// rotations), rescale scratch.
 struct RotWs {
   uint32_t *T, *D, *acc, *tmp;
   void* rs;
@@ -764,9 +801,9 @@ hipError_t launch_rotate_seq(const Tables& t, const uint32_t* ct, Seq in_seq, ui
     switch (t.log_n) {
 #define CKKS_MODUP2(LN)                                                                           \
   case LN:                                                                                        \
-    modup_intt_kernel<LN><<<inputs * L, WholePlan<LN>::P::T, 0, s>>>(t, ct, in_seq, L, w.T);      \
+    modup_intt_kernel<LN><<<inputs * L, WholePlan<LN, true>::P::T, 0, s>>>(t, ct, in_seq, L, w.T);      \
     if ((err = hipGetLastError()) != hipSuccess) return err;                                      \
-    modup_ntt_kernel<LN><<<grid, WholePlan<LN>::P::T, 0, s>>>(t, ct, in_seq, w.T, L, w.D);        \
+    modup_ntt_kernel<LN><<<grid, WholePlan<LN, true>::P::T, 0, s>>>(t, ct, in_seq, w.T, L, w.D);        \
     break;
       CKKS_MODUP2(10)
       CKKS_MODUP2(11)
@@ -805,12 +842,18 @@ hipError_t launch_rotate_seq(const Tables& t, const uint32_t* ct, Seq in_seq, ui
     const uint32_t copies = copy_inputs ? inputs : 0;
     const Seq cseq = copy_inputs ? *copy_inputs : contiguous();
     const dim3 grid(2 * (rotations + copies), L);
+    const bool stored = static_cast<size_t>(2) * rotations * L >= 3 * static_cast<size_t>(t.num_cus);
     switch (t.log_n) {
-#define CKKS_MDC(LN)                                                                                       \
-  case LN:                                                                                                 \
-    moddown_combine_kernel<LN><<<grid, WholePlan<LN, true>::P::T, 0, s>>>(t, w.acc, ct, in_seq, L, rotations, \
-                                                                          plan, out, out_seq, cseq);       \
-    break;
+#define CKKS_MDC(LN)                                                                                              \
+  case LN: {                                                                                                      \
+    constexpr uint32_t T = WholePlan<LN, true>::P::T;                                                             \
+    if (stored) {                                                                                                 \
+      moddown_inv_kernel<LN><<<2 * rotations, T, 0, s>>>(t, w.acc, L, w.tmp);                                     \
+      if ((err = hipGetLastError()) != hipSuccess) return err;                                                    \
+    }                                                                                                             \
+    const auto combine = stored ? moddown_combine_kernel<LN, true> : moddown_combine_kernel<LN, false>;           \
+    combine<<<grid, T, 0, s>>>(t, w.acc, w.tmp, ct, in_seq, L, rotations, plan, out, out_seq, cseq);              \
+  } break;
       CKKS_MDC(10)
       CKKS_MDC(11)
       CKKS_MDC(12)

@@ -1,6 +1,7 @@
 """Edges of size rules: the smallest and odd row counts of the 2^15 inverse transform whose
-workgroups walk the rows, the poly MAC on both sides of its rows-per-thread rule, and the
-encoder with coefficients on both sides of 2^31."""
+workgroups walk the rows, the poly MAC on both sides of its rows-per-thread rule, the
+encoder with coefficients on both sides of 2^31, and rotations on both sides of the rule that
+splits ModDown."""
 import numpy as np
 import pytest
 
@@ -85,4 +86,27 @@ def test_encode_coefficients_around_int32(gpu_lib, log_n, top):
         diff = np.mod(coef - np.mod(want, q).astype(np.int64), q)
         off = diff != 0
         assert np.all((diff[off] == 1) | (diff[off] == q - 1)) and off.sum() <= most, (l, off.sum(), most)
+    ctx.close()
+
+
+@pytest.mark.parametrize("log_n,L,count,small", [(10, 4, 128, 127), (11, 5, 97, 48), (13, 5, 96, 95), (14, 3, 192, 100)])
+@pytest.mark.parametrize("hoisted", [True, False])
+def test_many_rotations_equal_few(gpu_lib, log_n, L, count, small, hoisted):
+    """ModDown in two launches (at least three workgroups a CU) against the one-launch form
+    of the same rotations in smaller calls, which the oracle covers."""
+    ck = gpu_lib
+    ctx = ck.Context(log_n, L)
+    n, lk, qs = ctx.n, L - 1, ctx.moduli
+    assert 2 * small * lk < 3 * 256 <= 2 * count * lk
+    rng = np.random.default_rng(log_n * 100 + count)
+    ct = ck.to_device(gen.uniform_residues(rng, (1 if hoisted else count, 2), qs[:lk], n))
+    ksk = ck.to_device(gen.uniform_residues(rng, (count, lk, 2), qs, n))
+    got, ref = ck.empty_u32((count, 2, lk, n)), ck.empty_u32((count, 2, lk, n))
+    got.fill_(-1)
+    ws = ck.empty_workspace(ck.rotate_workspace_bytes(ctx, count, hoisted))
+    ck.ckks_rotate(ctx, ct, count, 3, 5, hoisted, ksk, ws, got)
+    for k in range(0, count, small):
+        m = min(small, count - k)
+        ck.ckks_rotate(ctx, ct if hoisted else ct[k:k + m], m, 3 + 5 * k, 5, hoisted, ksk[k:k + m], ws, ref[k:k + m])
+    assert np.array_equal(ck.to_host_u32(got), ck.to_host_u32(ref))
     ctx.close()
