@@ -122,10 +122,10 @@ __device__ __forceinline__ uint32_t reduce_f64_int(double v, uint32_t q, double 
 // rows[][N] (gstride 0 means limbs: packed [count][limbs][N]).
 hipError_t launch_ntt(const Tables& t, uint32_t* rows, size_t count_rows, uint32_t limbs,
                       bool inverse, hipStream_t s, uint32_t gstride = 0);
-// The column pass alone of the inverse transform at N = 2^16, of rows whose
-// block pass is done.
-hipError_t launch_intt16_cols(const Tables& t, uint32_t* rows, size_t count_rows, uint32_t limbs, uint32_t gstride,
-                              hipStream_t s);
+// The column pass alone of a transform at N = 2^16: the forward's first pass (the
+// rows are left in the lazy range [0, 4q)), the inverse's last.
+hipError_t launch_ntt16_cols(const Tables& t, uint32_t* rows, size_t count_rows, uint32_t limbs, bool inverse,
+                             hipStream_t s, uint32_t gstride);
 
 hipError_t launch_encode_scalar(const Tables& t, const double* w, size_t count, uint32_t limbs,
                                 double scale, uint32_t* w_enc, hipStream_t s);

@@ -220,10 +220,11 @@ hipError_t launch_ntt16(const Tables& t, uint32_t* rows, size_t count, uint32_t 
 
 }  // namespace
 
-hipError_t launch_intt16_cols(const Tables& t, uint32_t* rows, size_t count_rows, uint32_t limbs, uint32_t gstride,
-                              hipStream_t s) {
+hipError_t launch_ntt16_cols(const Tables& t, uint32_t* rows, size_t count_rows, uint32_t limbs, bool inverse,
+                             hipStream_t s, uint32_t gstride) {
   const uint32_t grid = static_cast<uint32_t>(count_rows * ((1 << (16 - kColLogE)) / kColThreads));
-  ntt16_cols_kernel<true><<<grid, kColThreads, 0, s>>>(t, rows, limbs, gstride);
+  const auto cols = inverse ? ntt16_cols_kernel<true> : ntt16_cols_kernel<false>;
+  cols<<<grid, kColThreads, 0, s>>>(t, rows, limbs, gstride);
   return hipGetLastError();
 }
 

@@ -13,21 +13,40 @@
 //
 // Encryption and decryption, up to N = 2^15, are one kernel each: the error's
 // residues (or c0 + c1 (.) s) are formed as the transform loads its row and the
-// combine (or the coefficients) leave with its stores, 256 workgroups and more
-// running as the batched transforms do.  At 2^16 (a row exceeds the LDS) the same
+// combine (or the coefficients) leave with its stores.  At 2^16 (a row exceeds the LDS) the same
 // work rides on the first and last passes of the staged transforms.  100
 // features at 2^16 and 8 limbs, encoded, encrypted and decrypted: 1065 -> 815 us
 // (separate error, transform and pointwise passes before; the encoding, 400 us,
-// is the same in both).  The refresh, up to N = 2^15, is two transform kernels
+// is the same in both); 500 of 2^14 and 4 limbs 478 -> 322 us.  These kernels and
+// the refresh's run on the latency plan at every count: their loads and Barrett
+// products beside the butterflies gain more from twice the waves a SIMD than
+// the butterflies lose to a fourth group (the 768-ciphertext refresh at 2^14 325
+// -> 313 us, 32 ciphertexts 39 -> 35 us).  The refresh, up to N = 2^15, is two transform kernels
 // (decrypt + inverse, lift + forward + combine), or up to 2^13 for decode-size
 // counts one fused kernel split by output limb; at 2^16 the staged passes of
-// decryption and encryption with the lift in the column pass's loads.
+// decryption and encryption around the lift.
 #include <type_traits>
 
 #include "ntt_core.hpp"
 
 namespace ckks {
 namespace {
+
+constexpr int kThreads = 256;  // pointwise kernels
+
+// Signed 64-bit x mod q, in [0, q).
+__device__ __forceinline__ uint32_t reduce_i64(int64_t x, uint32_t q, double qr) {
+  const uint64_t ax = static_cast<uint64_t>(x < 0 ? -x : x);
+  const uint32_t r = reduce_u64(ax, q, qr);
+  return (x < 0 && r != 0) ? q - r : r;
+}
+
+// 16-byte accesses use native vector types.
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef int32_t v4s __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4u ld4(const uint32_t* p) { return *reinterpret_cast<const v4u*>(p); }
+__device__ __forceinline__ v4s ld4(const int32_t* p) { return *reinterpret_cast<const v4s*>(p); }
+__device__ __forceinline__ void st4(uint32_t* p, v4u v) { *reinterpret_cast<v4u*>(p) = v; }
 
 // floor(w 2^32 / q) for w < q (the Shoup companion of w): the fp64 estimate is
 // within one of it, and one remainder check fixes it.
@@ -180,12 +199,12 @@ __global__ __launch_bounds__(RefreshPlan<LOGN>::P::T, RefreshPlan<LOGN>::kWavesP
 //     the value mod q_l plus the fresh error, the forward transform, and
 //     c0 = . - a (.) s written coalesced;
 // c1 = a: rows from 2 on by (2), rows 0 and 1 (the scratch) copied afterwards.
-template <int LOGN, bool LAT>
-__global__ __launch_bounds__((WholePlan<LOGN, LAT>::P::T), (WholePlan<LOGN, LAT>::kWavesPerSimd)) void dec_intt_kernel(
+template <int LOGN>
+__global__ __launch_bounds__((WholePlan<LOGN, true>::P::T), (WholePlan<LOGN, true>::kWavesPerSimd)) void dec_intt_kernel(
     Tables tb, const uint32_t* __restrict__ ct_in, uint32_t limbs_in, const uint32_t* __restrict__ s_ntt,
     uint32_t limbs_used, uint32_t* __restrict__ out, uint32_t out_gstride) {
-  using P = typename WholePlan<LOGN, LAT>::P;
-  constexpr int LOGE = WholePlan<LOGN, LAT>::LOGE;
+  using P = typename WholePlan<LOGN, true>::P;
+  constexpr int LOGE = WholePlan<LOGN, true>::LOGE;
   constexpr int N = P::B;
   __shared__ uint32_t lds[P::lds_words];
   const size_t c = blockIdx.x / limbs_used;
@@ -214,11 +233,11 @@ __global__ __launch_bounds__((WholePlan<LOGN, LAT>::P::T), (WholePlan<LOGN, LAT>
 }
 
 template <int LOGN>
-__global__ __launch_bounds__((WholePlan<LOGN>::P::T), (WholePlan<LOGN>::kWavesPerSimd)) void dte_lift_ntt_kernel(
+__global__ __launch_bounds__((WholePlan<LOGN, true>::P::T), (WholePlan<LOGN, true>::kWavesPerSimd)) void dte_lift_ntt_kernel(
     Tables tb, const int32_t* __restrict__ e, const uint32_t* __restrict__ s_ntt, const uint32_t* __restrict__ a,
     uint32_t limbs_out, uint32_t* __restrict__ ct_out) {
-  using P = typename WholePlan<LOGN>::P;
-  constexpr int LOGE = WholePlan<LOGN>::LOGE;
+  using P = typename WholePlan<LOGN, true>::P;
+  constexpr int LOGE = WholePlan<LOGN, true>::LOGE;
   constexpr int N = P::B;
   __shared__ uint32_t lds[P::lds_words];
   // logical id = c * limbs_out + l.  Consecutive workgroup ids alternate XCDs, so
@@ -354,12 +373,12 @@ __device__ __forceinline__ void combine_row(const uint32_t (&v)[E], const RowAt&
 // 5 row transfers (e from L2 for all limbs but one) where error rows, a batched
 // transform and a pointwise pass took 8.  The limbs of a ciphertext run
 // together on one XCD and read its error row from HBM once.
-template <int LOGN, bool LAT, bool kPt>
-__global__ __launch_bounds__((WholePlan<LOGN, LAT>::P::T), (WholePlan<LOGN, LAT>::kWavesPerSimd)) void encrypt_kernel(
+template <int LOGN, bool kPt>
+__global__ __launch_bounds__((WholePlan<LOGN, true>::P::T), (WholePlan<LOGN, true>::kWavesPerSimd)) void encrypt_kernel(
     Tables tb, const uint32_t* __restrict__ pt, const uint32_t* __restrict__ s_ntt, const uint32_t* __restrict__ a,
     const int32_t* __restrict__ e, uint32_t limbs, uint32_t* __restrict__ ct) {
-  using P = typename WholePlan<LOGN, LAT>::P;
-  constexpr int LOGE = WholePlan<LOGN, LAT>::LOGE;
+  using P = typename WholePlan<LOGN, true>::P;
+  constexpr int LOGE = WholePlan<LOGN, true>::LOGE;
   constexpr int N = P::B;
   __shared__ uint32_t lds[P::lds_words];
   const uint32_t G = gridDim.x;
@@ -386,8 +405,8 @@ __global__ __launch_bounds__((WholePlan<LOGN, LAT>::P::T), (WholePlan<LOGN, LAT>
 
 // ---- N = 2^16 (a row exceeds the LDS): the transforms' column and block passes
 // of the batched kernels with the pointwise work folded into their first loads
-// and last stores.  A column pass over the error (or the lifted refresh value)
-// forms each limb's residues as it loads; a block pass combines as it stores.
+// and last stores.  A column pass over the error forms each limb's residues as it
+// loads; a block pass combines as it stores.
 // Decryption's block pass forms c0 + c1 (.) s as it loads.  6 row transfers per
 // limb for an encryption (10 with separate passes), 5 for a decryption (7).
 constexpr int kColLogE = 6;
@@ -397,14 +416,11 @@ constexpr int kBlkLogB = 10;
 constexpr int kBlkLogE = 4;
 constexpr int kBlocksPerRow = 1 << (16 - kBlkLogB);
 
-// Column pass of row (c, l): kLift false, v = e mod q_l; kLift true, the CRT value
-// of the two rows at `dec` (residues mod q0, q1) plus e, mod q_l.  Written to row
-// c * gstride + l of `out`, in the lazy range.  The limbs of one ciphertext are
-// numbered together on one XCD and share the rows they read.
-template <bool kLift>
-__global__ __launch_bounds__(kColThreads, 2) void rlwe16_cols_kernel(Tables tb, const int32_t* __restrict__ e,
-                                                                     const uint32_t* dec, uint32_t limbs,
-                                                                     uint32_t gstride, uint32_t* out) {
+// Column pass of the c0 row (c, l) of ct [count][2][limbs][N], from the error, left
+// in the lazy range.  The limbs of one ciphertext are numbered together on one
+// XCD and share the error row.
+__global__ __launch_bounds__(kColThreads, 2) void enc16_cols_kernel(Tables tb, const int32_t* __restrict__ e,
+                                                                    uint32_t limbs, uint32_t* __restrict__ ct) {
   using P = Plan<16, kColLogE>;
   const uint32_t G = gridDim.x;
   uint32_t lid = blockIdx.x;
@@ -415,29 +431,66 @@ __global__ __launch_bounds__(kColThreads, 2) void rlwe16_cols_kernel(Tables tb, 
   const uint32_t q = tb.q[l];
   const int32_t* ec = e + (c << 16) + col;
   uint32_t v[P::E];
-  if constexpr (kLift) {
-    const uint32_t* d0 = dec + ((c * gstride) << 16) + col;
-    const uint32_t q0 = tb.q[0], q1 = tb.q[1];
-    const uint32_t w = tb.qinv[0 * tb.L + 1], ws = tb.qinv_shoup[0 * tb.L + 1];  // q0^-1 mod q1
-    const uint64_t half = static_cast<uint64_t>(q0) * q1 / 2;
-    const LiftConst lc = lift_const(q0, q1, q, tb.q_recip[l]);
 #pragma unroll
-    for (int j = 0; j < P::E; ++j) {
-      const uint32_t o = P::template pos<0>(0, j);
-      const uint32_t x0 = d0[o], r0m = x0 >= q1 ? x0 - q1 : x0;
-      const uint32_t k = mul_shoup(sub_mod(d0[65536 + o], r0m, q1), w, ws, q1);
-      const bool neg = static_cast<uint64_t>(x0) + static_cast<uint64_t>(q0) * k > half;
-      v[j] = lift_residue(lc, x0, k, neg, ec[o]);
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < P::E; ++j) v[j] = small_residue(ec[P::template pos<0>(0, j)], q);
-  }
+  for (int j = 0; j < P::E; ++j) v[j] = small_residue(ec[P::template pos<0>(0, j)], q);
   const size_t tl = static_cast<size_t>(l) << 16;
   fwd_group<16, 16, kColLogE, 0>(v, col, 0, tb.fwd + tl, tb.fwd_shoup + tl, q);  // [0, 4q)
-  uint32_t* o = out + ((c * gstride + l) << 16) + col;
+  uint32_t* o = ct + (((c * 2) * limbs + l) << 16) + col;
 #pragma unroll
   for (int j = 0; j < P::E; ++j) __builtin_nontemporal_store(v[j], &o[P::template pos<0>(0, j)]);
+}
+
+// Thread -> (ciphertext c, coefficient quad k4) over count * N/4 quads.
+struct Quad {
+  size_t c;
+  uint32_t k;
+  bool ok;
+};
+__device__ __forceinline__ Quad quad_of(uint32_t n, uint32_t count) {
+  const size_t i = static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x;
+  const uint32_t per = n >> 2;
+  Quad r;
+  r.c = i / per;
+  r.k = static_cast<uint32_t>(i % per) * 4;
+  r.ok = r.c < count;
+  return r;
+}
+
+// Refresh lift.  dec rows (c * 2 limbs_out + limbs_out + {0, 1}) hold the
+// decrypted coefficient residues mod q0, q1.  x = r0 + q0 ((r1 - r0) q0^-1
+// mod q1) is the CRT value in [0, q0 q1); centred, plus the fresh error, it
+// is written mod q_l into the c0 rows of ct_out for l < limbs_out.
+__global__ __launch_bounds__(kThreads) void dte_lift_kernel(Tables tb, const int32_t* __restrict__ e,
+                                                            uint32_t count, uint32_t limbs_out,
+                                                            uint32_t* __restrict__ ct_out) {
+  const uint32_t n = tb.n;
+  const Quad p = quad_of(n, count);
+  if (!p.ok) return;
+  const uint32_t q0 = tb.q[0], q1 = tb.q[1];
+  const uint32_t w = tb.qinv[0 * tb.L + 1], ws = tb.qinv_shoup[0 * tb.L + 1];  // q0^-1 mod q1
+  const uint64_t Q2 = static_cast<uint64_t>(q0) * q1;
+  const uint32_t* d0 = ct_out + ((p.c * 2) * limbs_out + limbs_out) * n + p.k;
+  const v4u r0v = ld4(d0);
+  const v4u r1v = ld4(d0 + n);
+  const v4s ev = ld4(e + p.c * n + p.k);
+  int64_t m[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t r0 = r0v[j];
+    const uint32_t r0m = r0 >= q1 ? r0 - q1 : r0;  // r0 < q0 < 2 q1
+    const uint32_t t = mul_shoup(sub_mod(r1v[j], r0m, q1), w, ws, q1);
+    const uint64_t x = static_cast<uint64_t>(r0) + static_cast<uint64_t>(q0) * t;  // [0, q0 q1)
+    const int64_t xc = x > Q2 / 2 ? static_cast<int64_t>(x) - static_cast<int64_t>(Q2) : static_cast<int64_t>(x);
+    m[j] = xc + ev[j];
+  }
+  for (uint32_t l = 0; l < limbs_out; ++l) {
+    const uint32_t q = tb.q[l];
+    const double qr = tb.q_recip[l];
+    v4u o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = reduce_i64(m[j], q, qr);
+    st4(ct_out + ((p.c * 2) * limbs_out + l) * n + p.k, o);
+  }
 }
 
 // Block pass of the c0 rows of ct [count][2][limbs][N], in place, with the combine.
@@ -499,30 +552,18 @@ __global__ __launch_bounds__(1 << (kBlkLogB - kBlkLogE)) void dec16_blocks_kerne
   for (int j = 0; j < P::E; ++j) __builtin_nontemporal_store(v[j], &o[P::template pos<0>(t, j)]);
 }
 
-// Fewer rows than CUs take the latency plan (2^13 and 2^14), as the batched transforms.
 template <int LOGN>
 hipError_t launch_encrypt_whole(const Tables& t, const uint32_t* pt, const uint32_t* s_ntt, const uint32_t* a,
                                 const int32_t* e, uint32_t count, uint32_t limbs, uint32_t* ct, hipStream_t s) {
-  const uint32_t rows = count * limbs;
-  auto go = [&](auto lat) {
-    constexpr bool kLat = decltype(lat)::value;
-    constexpr uint32_t T = WholePlan<LOGN, kLat>::P::T;
-    if (pt) encrypt_kernel<LOGN, kLat, true><<<rows, T, 0, s>>>(t, pt, s_ntt, a, e, limbs, ct);
-    else encrypt_kernel<LOGN, kLat, false><<<rows, T, 0, s>>>(t, pt, s_ntt, a, e, limbs, ct);
-  };
-  if ((LOGN == 13 || LOGN == 14) && rows < t.num_cus) go(std::true_type{});
-  else go(std::false_type{});
+  const auto k = pt ? encrypt_kernel<LOGN, true> : encrypt_kernel<LOGN, false>;
+  k<<<count * limbs, WholePlan<LOGN, true>::P::T, 0, s>>>(t, pt, s_ntt, a, e, limbs, ct);
   return hipGetLastError();
 }
 
 template <int LOGN>
 hipError_t launch_decrypt_whole(const Tables& t, const uint32_t* ct, const uint32_t* s_ntt, uint32_t count,
                                 uint32_t limbs, uint32_t* m, hipStream_t s) {
-  const uint32_t rows = count * limbs;
-  if ((LOGN == 13 || LOGN == 14) && rows < t.num_cus)
-    dec_intt_kernel<LOGN, true><<<rows, WholePlan<LOGN, true>::P::T, 0, s>>>(t, ct, limbs, s_ntt, limbs, m, limbs);
-  else
-    dec_intt_kernel<LOGN, false><<<rows, WholePlan<LOGN>::P::T, 0, s>>>(t, ct, limbs, s_ntt, limbs, m, limbs);
+  dec_intt_kernel<LOGN><<<count * limbs, WholePlan<LOGN, true>::P::T, 0, s>>>(t, ct, limbs, s_ntt, limbs, m, limbs);
   return hipGetLastError();
 }
 
@@ -530,8 +571,8 @@ template <int LOGN>
 hipError_t launch_refresh_two(const Tables& t, const uint32_t* ct_in, uint32_t limbs_in, const uint32_t* s_ntt,
                               const uint32_t* a, const int32_t* e, uint32_t count, uint32_t limbs_out,
                               uint32_t* ct_out, hipStream_t s) {
-  constexpr uint32_t T = WholePlan<LOGN>::P::T;
-  dec_intt_kernel<LOGN, false><<<dim3(2 * count), T, 0, s>>>(
+  constexpr uint32_t T = WholePlan<LOGN, true>::P::T;
+  dec_intt_kernel<LOGN><<<dim3(2 * count), T, 0, s>>>(
       t, ct_in, limbs_in, s_ntt, 2, ct_out + static_cast<size_t>(limbs_out) * t.n, 2 * limbs_out);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
@@ -566,7 +607,7 @@ hipError_t launch_encrypt(const Tables& t, const uint32_t* pt, const uint32_t* s
     default: break;
   }
   const uint32_t rows = count * limbs;
-  rlwe16_cols_kernel<false><<<rows * kColBlocks, kColThreads, 0, s>>>(t, e, nullptr, limbs, 2 * limbs, ct);
+  enc16_cols_kernel<<<rows * kColBlocks, kColThreads, 0, s>>>(t, e, limbs, ct);
   const auto blocks = pt ? rlwe16_blocks_combine_kernel<true> : rlwe16_blocks_combine_kernel<false>;
   blocks<<<rows * kBlocksPerRow, 1 << (kBlkLogB - kBlkLogE), 0, s>>>(t, pt, s_ntt, a, limbs, ct);
   return hipGetLastError();
@@ -585,7 +626,7 @@ hipError_t launch_decrypt(const Tables& t, const uint32_t* ct, const uint32_t* s
   }
   dec16_blocks_kernel<<<count * limbs * kBlocksPerRow, 1 << (kBlkLogB - kBlkLogE), 0, s>>>(t, ct, limbs, s_ntt, limbs, m,
                                                                                           limbs);
-  return launch_intt16_cols(t, m, static_cast<size_t>(count) * limbs, limbs, limbs, s);
+  return launch_ntt16_cols(t, m, static_cast<size_t>(count) * limbs, limbs, true, s, limbs);
 }
 
 hipError_t launch_refresh(const Tables& t, const uint32_t* ct_in, uint32_t limbs_in, const uint32_t* s_ntt,
@@ -618,16 +659,22 @@ hipError_t launch_refresh(const Tables& t, const uint32_t* ct_in, uint32_t limbs
     default: break;
   }
   // N = 2^16: limbs 0 and 1 of c0 + c1 (.) s, inverse-transformed, in the c1 rows
-  // 0 and 1 of ct_out (scratch); the lift's column pass into the c0 rows; its
-  // block pass with the combine, which writes every c1 row.
+  // 0 and 1 of ct_out (scratch); the lift into the c0 rows (a pass of its own:
+  // in the column pass's loads every limb repeats it, 157 -> 216 us for 50
+  // ciphertexts of 4 limbs); the column pass; the block pass with the combine,
+  // which writes every c1 row.
   const uint32_t gs = 2 * limbs_out;
   uint32_t* dec = ct_out + static_cast<size_t>(limbs_out) * t.n;
   dec16_blocks_kernel<<<count * 2 * kBlocksPerRow, 1 << (kBlkLogB - kBlkLogE), 0, s>>>(t, ct_in, limbs_in, s_ntt, 2, dec,
                                                                                       gs);
-  const hipError_t err = launch_intt16_cols(t, dec, static_cast<size_t>(count) * 2, 2, gs, s);
+  hipError_t err = launch_ntt16_cols(t, dec, static_cast<size_t>(count) * 2, 2, true, s, gs);
   if (err != hipSuccess) return err;
+  const size_t quads = static_cast<size_t>(count) * (t.n / 4);
+  dte_lift_kernel<<<static_cast<uint32_t>((quads + kThreads - 1) / kThreads), kThreads, 0, s>>>(t, e, count, limbs_out,
+                                                                                               ct_out);
   const uint32_t rows = count * limbs_out;
-  rlwe16_cols_kernel<true><<<rows * kColBlocks, kColThreads, 0, s>>>(t, e, dec, limbs_out, gs, ct_out);
+  err = launch_ntt16_cols(t, ct_out, rows, limbs_out, false, s, gs);
+  if (err != hipSuccess) return err;
   rlwe16_blocks_combine_kernel<false><<<rows * kBlocksPerRow, 1 << (kBlkLogB - kBlkLogE), 0, s>>>(t, nullptr, s_ntt, a,
                                                                                                  limbs_out, ct_out);
   return hipGetLastError();

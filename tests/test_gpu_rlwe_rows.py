@@ -1,6 +1,6 @@
-"""Encryption and decryption at the edges of their dispatch: below and at one row per CU
-(the two plans of 2^13 and 2^14 rows), one limb, the largest whole-row ring, and the
-staged 2^16 form, each with and without a plaintext, against the oracle bit for bit."""
+"""Encryption and decryption below and above one row per CU, with one limb, at the largest
+whole-row ring and in the staged 2^16 form, each with and without a plaintext, against the
+oracle bit for bit."""
 import numpy as np
 import pytest
 
