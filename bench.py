@@ -1041,9 +1041,12 @@ def main():
     wdig = 3  # weight digits used by the MAC kernel for |round(w*scale)| <= 0x7f7f7f
     if np.max(np.abs(np.rint(W * cfg.scale))) > 0x7F7F7F:
         wdig = 4
-    ops_per_mac = 2 * wdig * 4
+    # four-digit weights of a large layer (2^40 products and more) go through eight int8
+    # residue channels instead of 4 x 4 digit products
+    channels = wdig == 4 and cfg.d_in <= 1024 and macs >= 1 << 40
+    ops_per_mac = 16 if channels else 2 * wdig * 4
     achieved = macs * ops_per_mac / (mac_ms * 1e-3)
-    traffic = traffic_from_profile(f"mac_mfma_{cfg.key}")
+    traffic = None if channels else traffic_from_profile(f"mac_mfma_{cfg.key}")
     out = {
         "metric": METRIC,
         "value": macs / (ms_per_step * 1e-3),
@@ -1062,12 +1065,14 @@ def main():
                    "step": "encode_scalar + mac_scalar (int8 MFMA) + rescale"},
         "roofline": {"bound": "mfma", "achieved": achieved / 1e12, "peak": MFMA_INT8_PEAK / 1e12,
                      "unit": "TFLOP/s", "frac": achieved / MFMA_INT8_PEAK, "traffic": traffic,
-                     "kernel": "ckks_linear_mac_scalar call: mfma_prep_kernel + "
-                               + ("mac_cs_kernel (column-stationary, d_in <= 1024)" if cfg.d_in <= 1024
-                                  else "mac_mfma_kernel (streamed)"),
+                     "kernel": "ckks_linear_mac_scalar call: "
+                               + ("rns_prep, rns_decide, rns_convert and rns_gemm kernels (eight residue channels)"
+                                  if channels else "mfma_prep_kernel + mac_cs_kernel (column-stationary, d_in <= 1024)"
+                                  if cfg.d_in <= 1024 else "mfma_prep_kernel + mac_mfma_kernel (streamed)"),
                      "algorithmic_bytes": cfg.d_in * 2 * L * n * 4 + cfg.d_out * 2 * L * n * 4
                      + cfg.d_out * cfg.d_in * L * 4,
-                     "work_per_launch": f"{macs:.4g} modMAC x {ops_per_mac} int8 ops ({wdig}x4 digit products)"},
+                     "work_per_launch": f"{macs:.4g} modMAC x {ops_per_mac} int8 ops "
+                                        + ("(8 residue channels)" if channels else f"({wdig}x4 digit products)")},
         "breakdown_ms": {"encode_scalar": enc_ms, "mac_scalar": mac_ms, "rescale": res_ms, "step_events": step_ms},
         "mac_only_modmac_per_s": macs / (mac_ms * 1e-3),
         "rescale_hbm_gbs": (cfg.d_out * 2 * (2 * L - 1) * n * 4) / (res_ms * 1e-3) / 1e9,
