@@ -38,7 +38,8 @@
 // takes more of here (192 bytes L2 -> LDS and 512 bytes LDS -> registers per
 // MFMA against 128 and 128).  Three-digit weights (12 products) are slower in
 // this form at every size measured, 58.1 against 53.0 ms at this shape, and
-// stay with the digit split.
+// stay with the digit split.  Four-digit weights are slower in it too where the
+// contraction is shallow or the space holds few rounds of workgroups (fit below).
 #include <type_traits>
 #include <utility>
 
@@ -240,19 +241,20 @@ __global__ __launch_bounds__(kPrepThreads) void rns_prep_kernel(
 
 // One workgroup: whether these kernels take the call (kRnsTaken) and, for every
 // limb and row, 2^29 sum v mod q.  They do when the weights are the same
-// integers in every limb, every row sum is within the bound, and at least half
-// of the 16-row tiles need a fourth weight digit: with three digits the digit
-// split takes 12 products with less operand traffic and is the faster.
+// integers in every limb, every row sum is within the bound, and at least
+// `wide_needed` of the 16-row tiles need a fourth weight digit: with three digits
+// the digit split takes 12 products with less operand traffic and is the faster.
 constexpr int kDecideThreads = 1024;
 __global__ __launch_bounds__(kDecideThreads) void rns_decide_kernel(Tables tb, const Part* __restrict__ part,
                                                                     uint32_t rows, uint32_t ks_total, uint32_t limbs,
-                                                                    uint64_t limit, uint32_t* __restrict__ rowc,
+                                                                    uint64_t limit, uint32_t wide_needed,
+                                                                    uint32_t* __restrict__ rowc,
                                                                     uint32_t* __restrict__ decision) {
   __shared__ uint32_t wide_tiles;
   if (threadIdx.x == 0) wide_tiles = 0;
   __syncthreads();
   uint32_t unfit = 0;
-  for (uint32_t r = threadIdx.x; r < rows; r += kDecideThreads) {  // rows is a multiple of 128
+  for (uint32_t r = threadIdx.x; r < rows; r += kDecideThreads) {  // rows is a multiple of kTM
     int64_t s = 0;
     uint64_t a = 0, marks = 0;
 #pragma unroll 8
@@ -273,7 +275,7 @@ __global__ __launch_bounds__(kDecideThreads) void rns_decide_kernel(Tables tb, c
     }
   }
   unfit = __syncthreads_or(unfit);
-  if (threadIdx.x == 0) *decision = !unfit && wide_tiles * 32 >= rows ? kRnsTaken : 0u;
+  if (threadIdx.x == 0) *decision = !unfit && wide_tiles >= wide_needed ? kRnsTaken : 0u;
 }
 
 // ---- ciphertext columns -------------------------------------------------------
@@ -530,15 +532,62 @@ __global__ __launch_bounds__(kThreads) void rns_gemm_kernel(
 
 uint32_t gcd(uint32_t a, uint32_t b) { return b ? gcd(b, a % b) : a; }
 
-// Strips per chunk for column planes of `room` bytes (0: these kernels do not
-// take the shape).  A chunk is whole rounds of one workgroup a CU where it can
-// be, and at least two rounds, so that a launch's last round and the gap before
-// the next one stay small beside it.
-uint32_t chunk_strips(const Tables& t, const Layout& s, uint32_t limbs, size_t room) {
-  const uint32_t total = limbs * (2 * t.n / kTN), round = t.num_cus / gcd(t.num_cus, s.rb);
+// Strips per chunk for column planes of `room` bytes (0: less than two rounds of
+// one workgroup a CU).  A chunk is whole rounds where it can be, and a multiple of
+// 8 workgroups, without which the contraction's tiles are not dealt out by XCD
+// (8193 x 1024, N = 2^14, 8 limbs: 23.7 ms with 191 strips, 19.7 with 184).
+uint32_t chunk_strips(const Tables& t, const Layout& s, uint32_t total, size_t room) {
+  const uint32_t round = t.num_cus / gcd(t.num_cus, s.rb);
   uint32_t strips = room / s.strip_bytes < total ? static_cast<uint32_t>(room / s.strip_bytes) : total;
-  if (strips < total && strips >= round) strips -= strips % round;
+  if (strips < total) strips -= strips % (strips >= round ? round : 8);
+  while (strips * s.rb % 8) --strips;
   return static_cast<size_t>(strips) * s.rb < 2 * t.num_cus ? 0 : strips;
+}
+
+// Whether the channels are worth trying on a shape, and if so how many 16-row
+// tiles of the weights have to need a fourth digit.
+//
+// Both forms' times in microseconds are fitted to 80 layers of four-digit weights
+// (d_out 300-12000, d_in 64-1024, N = 2^13-2^16, 2-16 limbs, 0.1-6.6e12
+// products; residuals mostly below 5%, at most 12%).  The channels take their time by rounds of
+// one 256 x 128 tile a CU, with a part that does not shrink with d_in (eight byte
+// reductions, the combine, the stores), the conversions, and two launches a
+// chunk; the digit split by 256-row steps of its 32-column workgroups.
+// Measured, digit split against channels, N = 2^16, 8 limbs: 6144 outputs of
+// d_in 1024 68.9 : 57.6 ms, 640 45.3 : 40.2, 384 29.9 : 29.3, 256 22.2 : 24.1,
+// 160 16.8 : 25.0; 2400 x 1000, whose chunks are 2.15 rounds, 26.6 : 31.4;
+// 8200 x 64 at 16 limbs 28.7 : 51.5.  The rule wants 8% by the fit, above its usual residual.
+//
+// Weights that turn out not to qualify lose the preparation and two empty
+// launches a chunk (3.7 us each) before the digit split: 53.2 -> 53.8 ms for
+// three-digit weights at 1024 -> 6144, but 27.1 -> 28.1 for 1024 -> 3072, whose
+// chunks are a quarter of that size.  Nothing on the host can tell, so the channels are
+// tried only where their gain is at least nine times that loss, and from 2^40
+// products up.
+struct Choice {
+  uint32_t chunk;        // strips per chunk, 0: the channels are not tried
+  uint32_t wide_needed;
+};
+Choice choose(const Tables& t, const Layout& s, uint32_t d_out, uint32_t d_in, uint32_t limbs, size_t room) {
+  const Choice no{0, 0};
+  if (static_cast<uint64_t>(d_out) * d_in * 2 * limbs * t.n < uint64_t{1} << 40) return no;
+  const uint32_t total = limbs * (2 * t.n / kTN);
+  const uint32_t chunk = chunk_strips(t, s, total, room);
+  if (chunk == 0) return no;
+  auto ceil_div = [](uint32_t a, uint32_t b) { return (a + b - 1) / b; };
+  const uint32_t full = total / chunk, last = total % chunk, chunks = full + (last != 0);
+  const double rounds = static_cast<double>(full) * ceil_div(chunk * s.rb, t.num_cus) + ceil_div(last * s.rb, t.num_cus);
+  const double rns = rounds * (3.28 * s.ks + 17.3) + 0.0094 * total * s.ks + 8.3 * chunks;
+  const uint32_t ks = ceil_div(d_in, 64);                                  // k-steps of the digit split
+  const double cols = ceil_div(limbs * (2 * t.n / 32), t.num_cus), steps = cols * ceil_div(d_out, 32) / 8.0;
+  const double mma = 1.2 * steps * ks, digit = mma + 2.1 * steps + 0.71 * cols * ks;
+  const double lost = 7.4 * chunks + 1.8e-4 * s.rows * s.ks * limbs + 30;  // launches, preparation and decision
+  const double gain = digit - 1.08 * rns;
+  if (gain < 0 || digit - rns < 9 * lost) return no;
+  // a tile of three-digit weights takes 12 of the 16 products
+  const uint32_t tiles = ceil_div(d_out, 16);
+  const double part = 1 - gain / (0.25 * mma);
+  return {chunk, static_cast<uint32_t>(ceil((part < 0.5 ? 0.5 : part) * tiles))};
 }
 
 uint64_t row_limit() {  // largest sum |v| of a row: 0.46 M / 2^29
@@ -572,11 +621,9 @@ hipError_t launch_mac_scalar_rns(const Tables& t, const uint32_t* w_enc, const u
                                  size_t workspace_bytes, uint32_t* decision, hipStream_t st, bool* launched) {
   *launched = false;
   const Layout s = layout_of(d_out, d_in, limbs);
-  // Below 2^40 products the weights' preparation, which is lost when they turn out
-  // not to qualify, is more than 1% of the call.
-  if (static_cast<uint64_t>(d_out) * d_in * 2 * limbs * t.n < uint64_t{1} << 40 || workspace_bytes <= s.strips)
-    return hipSuccess;
-  const uint32_t chunk = chunk_strips(t, s, limbs, workspace_bytes - s.strips);
+  if (workspace_bytes <= s.strips) return hipSuccess;
+  const Choice how = choose(t, s, d_out, d_in, limbs, workspace_bytes - s.strips);
+  const uint32_t chunk = how.chunk;
   if (chunk == 0) return hipSuccess;
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   Part* part = reinterpret_cast<Part*>(ws + s.part);
@@ -586,7 +633,8 @@ hipError_t launch_mac_scalar_rns(const Tables& t, const uint32_t* w_enc, const u
   const uint32_t total = limbs * (2 * t.n / kTN);
   rns_prep_kernel<<<dim3(s.rows / 16, s.ks), kPrepThreads, 0, st>>>(t.q, w_enc, d_out, d_in, limbs, s.rows, s.ks,
                                                                    aplanes, part);
-  rns_decide_kernel<<<1, kDecideThreads, 0, st>>>(t, part, s.rows, s.ks, limbs, row_limit(), rowc, decision);
+  rns_decide_kernel<<<1, kDecideThreads, 0, st>>>(t, part, s.rows, s.ks, limbs, row_limit(),
+                                             how.wide_needed, rowc, decision);
   for (uint32_t s0 = 0; s0 < total; s0 += chunk) {
     const uint32_t strips = total - s0 < chunk ? total - s0 : chunk;
     const size_t waves = static_cast<size_t>(strips) * 2 * s.ks * 4;
