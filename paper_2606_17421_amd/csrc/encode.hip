@@ -91,12 +91,13 @@ __device__ __forceinline__ void fft_pass(double2* a, int s, const double2* __res
 // operations an element ahead of its butterflies.  (Residues reduced to [0, q)
 // and scattered through the LDS for every limb before: 2.28 -> 2.02 ms for 4096
 // vectors of 2^15 x 6 limbs, 216 -> 202 us for 1024 of 2^14 x 4, 195 -> 175 us
-// for 2048 of 2^13 x 4.)  Otherwise the workgroup forms the coefficients again
-// from the spectrum, one at a time, writes every limb's residues to its output
-// rows and transforms the rows in place: kept in registers for this case, the
-// coefficients cost the common one its spills.  (Such vectors: 302 -> 260 us
-// for 1024 of 2^14 x 4 limbs, 58-65 -> 60-68 us for 2^12; kept below 2^13 only,
-// the common case at 2^11 went from 16.6 to 18.8 us for 500 vectors, 3 limbs.)
+// for 2048 of 2^13 x 4.)  Otherwise the workgroup writes every limb's residues
+// to its output rows and transforms the rows in place from there.  Below 2^13 the
+// rounded doubles stay in registers for that case; from 2^13 up, where they would
+// cost the common case its spills, the coefficients are formed again from the
+// spectrum, one at a time.  (Such vectors, formed again against kept: 500 of 2^12
+// x 3 limbs 27.3 : 25.2 us, 8000 of 2^11 x 3 160 : 147, 500 of 2^10 x 8 30.7 :
+// 26.8, the common case within 1%; 500 of 2^14 x 4 117 : 143.)
 template <int LOGN>
 struct FusedPlan {
   using W = WholePlan<LOGN>;
@@ -201,12 +202,17 @@ __global__ __launch_bounds__(FusedPlan<LOGN>::T, WholePlan<LOGN>::kWavesPerSimd)
   encode_spectrum<LOGN>(tb, z, spec);
   constexpr bool kKeep = LOGN >= 13;
   int32_t c[NP::E];
+  double p_lo[FP::KPT], p_hi[FP::KPT];  // not used from 2^13 up
   bool fits = true;
 #pragma unroll
   for (int i = 0; i < FP::KPT; ++i) {
     double lo, hi;
     fold_spectrum<LOGN>(tb, spec, scale, static_cast<int>(t) + T * i, lo, hi);
-    const bool ok = fmax(fabs(lo), fabs(hi)) < 2147483648.0;
+    if constexpr (!kKeep) {
+      p_lo[i] = lo;
+      p_hi[i] = hi;
+    }
+    const bool ok = fabs(lo) < 2147483648.0 && fabs(hi) < 2147483648.0;
     fits = fits && ok;
     c[i] = ok ? static_cast<int32_t>(lo) : 0;
     c[FP::KPT + i] = ok ? static_cast<int32_t>(hi) : 0;
@@ -252,6 +258,9 @@ __global__ __launch_bounds__(FusedPlan<LOGN>::T, WholePlan<LOGN>::kWavesPerSimd)
         __syncthreads();
 #pragma unroll
         for (int j = H; j < E; ++j) v[j] = static_cast<uint32_t>(own[T * j]);
+        // keeps the transform's twiddle loads below these reads: scheduled among
+        // them at 2^11, beside the doubles, they cost 8 limbs 22.8 -> 29.0 us
+        __builtin_amdgcn_sched_barrier(0);
       }
       const size_t tl = static_cast<size_t>(l) << LOGN;
       fwd_block<LOGN, LOGN, LOGE>(v, t, 0, tb.fwd + tl, tb.fwd_shoup + tl, q, lds);
@@ -261,15 +270,22 @@ __global__ __launch_bounds__(FusedPlan<LOGN>::T, WholePlan<LOGN>::kWavesPerSimd)
       for (int j = 0; j < E; ++j) __builtin_nontemporal_store(v[j], &row[j << 6]);
     }
   } else {
+    auto scatter = [&](uint32_t l, int i, double lo, double hi) {
+      uint32_t* row = out + static_cast<size_t>(l) * N;
+      scatter_residues<LOGN>([&](int x) -> uint32_t& { return row[x]; }, static_cast<int>(t) + T * i, lo, hi, tb.q[l],
+                             tb.q_recip[l]);
+    };
+    if constexpr (kKeep) {
 #pragma unroll 1
-    for (int i = 0; i < FP::KPT; ++i) {
-      double lo, hi;
-      fold_spectrum<LOGN>(tb, spec, scale, static_cast<int>(t) + T * i, lo, hi);
-      for (uint32_t l = 0; l < limbs; ++l) {
-        uint32_t* row = out + static_cast<size_t>(l) * N;
-        scatter_residues<LOGN>([&](int x) -> uint32_t& { return row[x]; }, static_cast<int>(t) + T * i, lo, hi, tb.q[l],
-                               tb.q_recip[l]);
+      for (int i = 0; i < FP::KPT; ++i) {
+        double lo, hi;
+        fold_spectrum<LOGN>(tb, spec, scale, static_cast<int>(t) + T * i, lo, hi);
+        for (uint32_t l = 0; l < limbs; ++l) scatter(l, i, lo, hi);
       }
+    } else {
+      for (uint32_t l = 0; l < limbs; ++l)
+#pragma unroll
+        for (int i = 0; i < FP::KPT; ++i) scatter(l, i, p_lo[i], p_hi[i]);
     }
     for (uint32_t l = 0; l < limbs; ++l) {
       __syncthreads();  // coefficient rows written; the previous transform is done with the LDS
