@@ -63,33 +63,29 @@ __global__ __launch_bounds__(kThreads) void mac_scalar_valu_kernel(
 // is read exactly once.  Workgroups with the same (l, slot block) and
 // consecutive row groups are adjacent in logical order, and each XCD runs a
 // contiguous range of logical ids, so the shared ciphertext columns are
-// fetched once into that XCD's L2.  Four rows per thread when the grid
-// still holds at least 2 workgroups per CU; narrower layers (a 32-output BSGS
-// giant-step set at 2^13) take two rows per thread for twice the workgroups.
-// A 16-group decode stack of 32 x 32, 4 limbs, N = 2^14, whose weights come from
-// HBM on every call: 2327 us with two rows, 2262 us with four.  Per input the
-// row loads are all issued before the first product (a ragged last group
-// re-reads row 0 for its missing rows and discards those sums), so a wave waits
-// on memory once per input instead of once per row: 31.1 -> 24.9 us at 32 x 32,
-// 2^13, 4 limbs (the next input's loads issued ahead of the products as well
-// gave nothing).  The plaintexts are read once and loaded non-temporally, so
-// that they displace neither the ciphertext columns that every row group
-// re-reads from L2 nor the last-level cache: 669 -> 623 us at 64 x 64, 2^15,
-// 6 limbs, 2397 -> 2327 us for the decode stack, 145 -> 140 us for a 1024 x 1024
-// BSGS product whose 134 MB of diagonals alternate with another's (only a loop
-// over the same diagonals, resident in the last-level cache, is slower with
-// them).  Outputs are stored non-temporally (written once): 621 -> 600 us at
-// 64 x 64, 2^15, 6 limbs; 53 -> 49.5 us at 32 x 32, 2^14, 4 limbs.
+// fetched once into that XCD's L2.  Per input the row loads are all issued before
+// the first product (a ragged last group re-reads row 0 for its missing rows and
+// discards those sums), so a wave waits on memory once per input instead of once
+// per row: 31.1 -> 24.9 us at 32 x 32, 2^13, 4 limbs (the next input's loads issued
+// ahead of the products as well gave nothing).  Outputs are stored
+// non-temporally (written once): 621 -> 600 us at 64 x 64, 2^15, 6 limbs; 53 ->
+// 49.5 us at 32 x 32, 2^14, 4 limbs.  launch_mac_poly chooses the rows per thread
+// and whether the plaintexts, each read once, pass the caches by.
 constexpr int kPolySlots = 4;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+template <bool kNonTemporal>
 __device__ __forceinline__ uint4 load_pt(const uint4* p) {
-  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-  return make_uint4(v.x, v.y, v.z, v.w);
+  if constexpr (kNonTemporal) {
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+  } else {
+    return *p;
+  }
 }
 
-template <int kPolyRows>
+template <int kPolyRows, bool kNonTemporal>
 __global__ __launch_bounds__(kThreads) void mac_poly_kernel(
     Tables tb, const uint32_t* __restrict__ pt, const uint32_t* __restrict__ ct_in,
     uint32_t* __restrict__ ct_out, uint32_t d_out, uint32_t d_in, uint32_t limbs) {
@@ -129,7 +125,7 @@ __global__ __launch_bounds__(kThreads) void mac_poly_kernel(
 #pragma unroll
       for (int r = 0; r < kPolyRows; ++r) {
         const uint32_t rr = r < rows ? r : 0;  // rows >= 1; sums of rows past d_out are not stored
-        pv[r] = load_pt(&p_ptr[rr * p_row + static_cast<size_t>(i) * ln4]);
+        pv[r] = load_pt<kNonTemporal>(&p_ptr[rr * p_row + static_cast<size_t>(i) * ln4]);
       }
       const uint32_t xs0[4] = {x0.x, x0.y, x0.z, x0.w}, xs1[4] = {x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
@@ -178,17 +174,39 @@ hipError_t launch_mac_scalar_valu(const Tables& t, const uint32_t* w_enc, const 
   return hipGetLastError();
 }
 
+// A call whose plaintexts fit the last-level cache (256 MiB) may find them there:
+// a product that is called again on the same weights.  Loaded plainly they stay,
+// non-temporally they do not, and a call over other weights each time, which
+// never finds its own, gains the other way round.  Nothing here tells the two
+// apart, so calls that fit load plainly, which costs neither of them against
+// loads that were always plain.  In us, the same plaintexts / others every call
+// (1.6 GB in turn):
+//                                     plain, 2 rows   non-temporal, 2 / 4 rows
+//   32 x 32, 2^13, 4 limbs (134 MB)   24.5 / 34.3     27.3 / 29.1   27.7 / 29.5
+//   24 x 32, 2^14, 4 limbs (201 MB)   36.3 / 44.8     39.5 / 40.0   46.7 / 48.1
+//   8 x 96, 2^12, 3 limbs (38 MB)     39.8 / 58.3     50.7 / 55.7   63.2 / 67.1
+//   32 x 32, 2^14, 4 limbs (268 MB)   49.6 / 59.6     52.5 / 53.0   48.5 / 49.1
+//   64 x 16, 2^14, 4 limbs (268 MB)   54.1 / 66.2     57.9 / 59.9   68.5 / 70.7
+//   80 x 14, 2^14, 4 limbs (294 MB)   63.5 / 67.8     62.9 / 64.4   59.5 / 61.0
+//   64 x 80, 2^12, 4 limbs (336 MB)   69.4 / 69.1     63.7 / 64.7   68.5 / 69.1
+//   24 x 80, 2^15, 4 limbs (1 GB)     212 / 212       196 / 196     167 / 167
+// From 8 workgroups a CU four rows are the faster whatever the size (256 x 16,
+// 2^13, 4 limbs: 101.6 us against 111 with two, non-temporal both, and 117 plain).
+// Three of the four-row kernel's workgroups fit a CU (130 registers): just past
+// the cache, where part of the plaintexts may still be found, a grid of two or
+// three a CU gains in both columns and a larger one need not; below two, two rows
+// fill the chip better.
 hipError_t launch_mac_poly(const Tables& t, const uint32_t* pt, const uint32_t* ct_in,
                            uint32_t* ct_out, uint32_t d_out, uint32_t d_in, uint32_t limbs,
                            hipStream_t s) {
-  const size_t blocks = static_cast<size_t>(limbs) * (t.n / (kThreads * kPolySlots));
-  const size_t grid4 = static_cast<size_t>((d_out + 3) / 4) * blocks;
-  if (grid4 >= 2 * static_cast<size_t>(t.num_cus)) {
-    mac_poly_kernel<4><<<static_cast<uint32_t>(grid4), kThreads, 0, s>>>(t, pt, ct_in, ct_out, d_out, d_in, limbs);
-  } else {
-    const size_t grid2 = static_cast<size_t>((d_out + 1) / 2) * blocks;
-    mac_poly_kernel<2><<<static_cast<uint32_t>(grid2), kThreads, 0, s>>>(t, pt, ct_in, ct_out, d_out, d_in, limbs);
-  }
+  constexpr size_t kCache = size_t(256) << 20, kPast = size_t(288) << 20;
+  const size_t bytes = static_cast<size_t>(d_out) * d_in * limbs * t.n * 4;
+  const size_t blocks = static_cast<size_t>(limbs) * (t.n / (kThreads * kPolySlots)), cus = t.num_cus;
+  const size_t grid4 = (static_cast<size_t>(d_out) + 3) / 4 * blocks, grid2 = (static_cast<size_t>(d_out) + 1) / 2 * blocks;
+  const bool four = grid4 >= 8 * cus || (grid4 >= 2 * cus && (bytes >= kPast || (bytes >= kCache && grid4 <= 3 * cus)));
+  const uint32_t grid = static_cast<uint32_t>(four ? grid4 : grid2);
+  const auto mac = four ? mac_poly_kernel<4, true> : bytes >= kPast ? mac_poly_kernel<2, true> : mac_poly_kernel<2, false>;
+  mac<<<grid, kThreads, 0, s>>>(t, pt, ct_in, ct_out, d_out, d_in, limbs);
   return hipGetLastError();
 }
 

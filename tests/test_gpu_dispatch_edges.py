@@ -1,5 +1,5 @@
 """Edges of size rules: the smallest and odd row counts of the 2^15 inverse transform whose
-workgroups walk the rows, the poly MAC on both sides of its rows-per-thread rule, the
+workgroups walk the rows, the poly MAC on both sides of its rules for rows and loads, the
 encoder with coefficients on both sides of 2^31, and rotations on both sides of the rule that
 splits ModDown."""
 import numpy as np
@@ -35,23 +35,39 @@ def test_intt_walk_n15(gpu_lib, limbs, count):
     ctx.close()
 
 
-@pytest.mark.parametrize("d_out", [27, 28, 29, 30, 32, 33])
-def test_mac_poly_rows_per_thread(gpu_lib, d_out):
-    """N = 2^14, 4 limbs: 29 outputs are the fewest that take four rows a thread."""
+@pytest.mark.parametrize("log_n,limbs,d_out,d_in", [
+    (14, 4, 27, 17), (14, 4, 28, 17), (14, 4, 29, 17), (14, 4, 30, 17), (14, 4, 32, 17), (14, 4, 33, 17),
+    (14, 4, 32, 31), (14, 4, 32, 32),       # 2 groups of four rows a CU: below 256 MiB of plaintexts, and 256 MiB
+    (14, 4, 31, 34), (14, 4, 48, 22),       # ragged, and 3 a CU
+    (14, 4, 49, 21),                        # past 256 MiB, more than 3 a CU
+    (14, 4, 28, 41), (14, 4, 28, 42),       # fewer than 2 a CU: below and past 288 MiB
+    (14, 4, 49, 25),                        # past 288 MiB, more than 3 a CU
+    (14, 16, 28, 3), (14, 16, 29, 3),       # 7 and 8 a CU
+])
+def test_mac_poly_rows_per_thread(gpu_lib, log_n, limbs, d_out, d_in):
+    """Two rows a thread with plain and with non-temporal loads, and four rows, on both sides
+    of every line between them."""
+    import torch
     ck = gpu_lib
-    log_n, limbs, d_in = 14, 4, 17
     ctx = ck.Context(log_n, limbs)
     qs, n = ctx.moduli, ctx.n
-    rng = np.random.default_rng(d_out)
-    pt = gen.uniform_residues(rng, (d_out, d_in), qs, n)
-    ct = gen.uniform_residues(rng, (d_in, 2), qs, n)
-    pt[:, :, :, 0] = (np.array(qs, dtype=np.uint32) - 1)        # the largest sums
-    ct[:, :, :, 0] = (np.array(qs, dtype=np.uint32) - 1)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d_out * 100 + d_in)
+
+    def uniform(*shape):
+        x = torch.empty(shape + (limbs, n), dtype=torch.int32, device="cuda:0")
+        for l, q in enumerate(qs):
+            x[..., l, :] = torch.randint(0, q, shape + (n,), dtype=torch.int32, device="cuda:0", generator=g)
+            x[..., l, 0] = q - 1                                # the largest sums
+        return x
+
+    pt, ct = uniform(d_out, d_in), uniform(d_in, 2)
     out = ck.empty_u32((d_out, 2, limbs, n))
     out.fill_(-1)
-    ck.ckks_linear_mac_poly(ctx, ck.to_device(pt), ck.to_device(ct), out, d_out, d_in, limbs)
+    ck.ckks_linear_mac_poly(ctx, pt, ct, out, d_out, d_in, limbs)
     rows = sorted({0, 1, d_out // 2, d_out - 3, d_out - 2, d_out - 1})
-    assert np.array_equal(ck.to_host_u32(out)[rows], OL.mac_poly(pt, ct, qs, rows=rows).astype(np.uint32))
+    want = OL.mac_poly(ck.to_host_u32(pt[rows]), ck.to_host_u32(ct), qs).astype(np.uint32)
+    assert np.array_equal(ck.to_host_u32(out[rows]), want)
     ctx.close()
 
 
