@@ -376,8 +376,8 @@ __global__ __launch_bounds__(kThreads) void rot_combine_kernel(Tables tb, const 
 //     out[k] = (sigma_g(c0_m) + u0, u1),
 // the rescale's arithmetic (the P row is the last of the L + 1) with the
 // combine as its store, so u never goes through memory.  One workgroup per
-// polynomial acc[k][p] and output limb l (blockIdx.y).  Fewer than three
-// workgroups a CU each transform the P row themselves, in one launch; above,
+// polynomial acc[k][p] and output limb l (blockIdx.y).  Few workgroups each
+// transform the P row themselves, in one launch; where moddown_in_two says,
 // moddown_inv_kernel transforms every P row once and leaves r in T in the
 // plan's register order (kStored).  16 vectors of 1024 at 2^13, 4 limbs: 168 us
 // for the 496 rotations in one launch, 28 + 92 us in two (the call 771 -> 748
@@ -698,6 +698,18 @@ __global__ __launch_bounds__(kThreads) void bsgs_mac_tile_kernel(Tables tb, cons
   }
 }
 
+// ModDown in two launches: L - 1 of L transforms of every P row less, for a launch
+// and r's way through memory.  It pays from three workgroups a CU and 2.4 million
+// points of transforms less.  Hoisted rotations, the call in one launch : in two,
+// us: 256 of 2 limbs at 2^10 (0.5 million) 21.9 : 24.2, 256 of 2 at 2^11 (1.0) 30.9
+// : 33.1, 256 of 2 at 2^12 (2.1) 45.3 : 45.9, 192 of 4 at 2^11 (2.4) 44.9 : 44.2, 256
+// of 4 at 2^11 (3.1) 52.8 : 50.0, 192 of 2 at 2^13 (3.1) 64.5 : 64.6, 640 of 4 at 2^10
+// (3.9) 58.7 : 55.1, 96 of 6 at 2^13 (7.9) 117 : 105.
+bool moddown_in_two(const Tables& t, uint32_t L, uint32_t rotations) {
+  const size_t polys = static_cast<size_t>(2) * rotations;
+  return polys * L >= 3 * static_cast<size_t>(t.num_cus) && polys * (L - 1) * t.n >= 9216 * static_cast<size_t>(t.num_cus);
+}
+
 // Workspace of rotate(): T [inputs][L][N], D [inputs][L][L+1][N],
 // acc [rotations][2][L+1][N], tmp [rotations][2][L][N] (the separate ModDown's
 // output, 2^15 and 2^16; below, the inverse-transformed P rows of many
@@ -842,7 +854,7 @@ hipError_t launch_rotate_seq(const Tables& t, const uint32_t* ct, Seq in_seq, ui
     const uint32_t copies = copy_inputs ? inputs : 0;
     const Seq cseq = copy_inputs ? *copy_inputs : contiguous();
     const dim3 grid(2 * (rotations + copies), L);
-    const bool stored = static_cast<size_t>(2) * rotations * L >= 3 * static_cast<size_t>(t.num_cus);
+    const bool stored = moddown_in_two(t, L, rotations);
     switch (t.log_n) {
 #define CKKS_MDC(LN)                                                                                              \
   case LN: {                                                                                                      \

@@ -105,15 +105,19 @@ def test_encode_coefficients_around_int32(gpu_lib, log_n, top):
     ctx.close()
 
 
-@pytest.mark.parametrize("log_n,L,count,small", [(10, 4, 128, 127), (11, 5, 97, 48), (13, 5, 96, 95), (14, 3, 192, 100)])
+@pytest.mark.parametrize("log_n,L,count,small,two", [
+    (10, 4, 128, 127, False), (11, 5, 97, 48, False),                          # few points of transforms to save
+    (13, 5, 96, 95, True), (14, 3, 192, 100, True),                            # three workgroups a CU, and fewer
+    (10, 5, 384, 383, True), (11, 4, 288, 287, True), (12, 3, 288, 287, True)])  # just as many points, and fewer
 @pytest.mark.parametrize("hoisted", [True, False])
-def test_many_rotations_equal_few(gpu_lib, log_n, L, count, small, hoisted):
-    """ModDown in two launches (at least three workgroups a CU) against the one-launch form
-    of the same rotations in smaller calls, which the oracle covers."""
+def test_many_rotations_equal_few(gpu_lib, log_n, L, count, small, two, hoisted):
+    """A batch of rotations whose ModDown takes two launches (`two`) or one against the same
+    rotations in smaller calls of one launch, which the oracle covers."""
     ck = gpu_lib
     ctx = ck.Context(log_n, L)
     n, lk, qs = ctx.n, L - 1, ctx.moduli
-    assert 2 * small * lk < 3 * 256 <= 2 * count * lk
+    in_two = [2 * c * lk >= 3 * 256 and 2 * c * (lk - 1) * n >= 9216 * 256 for c in (count, small)]
+    assert in_two == [two, False]
     rng = np.random.default_rng(log_n * 100 + count)
     ct = ck.to_device(gen.uniform_residues(rng, (1 if hoisted else count, 2), qs[:lk], n))
     ksk = ck.to_device(gen.uniform_residues(rng, (count, lk, 2), qs, n))
