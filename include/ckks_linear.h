@@ -65,9 +65,12 @@ enum ckks_op {
 
 /* MAC kernel selection for ckks_linear_mac_scalar (ckks_ctx_set_mac_algo). */
 enum ckks_mac_algo {
-  CKKS_MAC_AUTO = 0, /* library choice (int8 MFMA digit split)               */
+  CKKS_MAC_AUTO = 0, /* library choice (int8 on the matrix cores, or VALU)   */
   CKKS_MAC_VALU = 1, /* u32 x u32 -> u64 vector multiply-add                 */
-  CKKS_MAC_MFMA = 2  /* exact int8 digit-split contractions on matrix cores  */
+  CKKS_MAC_MFMA = 2  /* exact int8 contractions on the matrix cores: base-256
+                        digits, or eight small residue channels for large
+                        layers of wide weights (chosen on the device; the
+                        result is the same)                                  */
 };
 
 /* Context: the RNS modulus chain of one ring degree and its device tables
@@ -149,9 +152,10 @@ int ckks_linear_mac_scalar(const ckks_ctx* ctx, const uint32_t* w_enc,
 /* ckks_linear_mac_scalar without a caller workspace, for callers that cannot
  * allocate device memory: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments, result and errors as
- * ckks_linear_mac_scalar; the matrix-core kernel's workspace (the weight digit
- * fragments and per-tile flags, ckks_workspace_bytes(ctx, CKKS_OP_MAC_SCALAR,
- * d_out, d_in, limbs) bytes) is instead a library-owned device array of
+ * ckks_linear_mac_scalar; the matrix-core kernels' workspace (the weight digit
+ * fragments and per-tile flags; a layer that the residue channels could take is
+ * too large for it; ckks_workspace_bytes(ctx, CKKS_OP_MAC_SCALAR, d_out, d_in,
+ * limbs) bytes) is instead a library-owned device array of
  * CKKS_NOALLOC_SCRATCH_BYTES (64 MiB) on each GPU the library runs on, held
  * until the process ends.  The call allocates nothing.  Requests needing more
  * scratch than that return CKKS_E_WORKSPACE (the fragments take 4 bytes per

@@ -207,7 +207,9 @@ modup_fused_kernel(Tables tb, const uint32_t* __restrict__ ct, Seq in_seq, uint3
 // One inverse transform per digit instead of one per (digit, prime) as in
 // modup_fused_kernel, whose workgroups then outnumber the CUs.  The latency plan
 // (twice the waves a SIMD) is the faster at every batch: 16 vectors of 1024 at
-// 2^13 748 -> 742 us a call, one 140.7 -> 139.0 us.
+// 2^13 748 -> 742 us a call, one 140.7 -> 139.0 us; with ModDown's kernels on it
+// too, rotations of 4 limbs, the other plan : this one, 31 at 2^13 57.9 : 52.4 us,
+// 256 at 2^13 291 : 282, 31 at 2^14 89.4 : 85.8, 256 at 2^14 592 : 572.
 template <int LOGN>
 __global__ __launch_bounds__((WholePlan<LOGN, true>::P::T), (WholePlan<LOGN, true>::kWavesPerSimd)) void modup_intt_kernel(
     Tables tb, const uint32_t* __restrict__ ct, Seq in_seq, uint32_t L, uint32_t* __restrict__ T) {

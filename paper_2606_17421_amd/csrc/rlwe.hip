@@ -20,11 +20,15 @@
 // is the same in both); 500 of 2^14 and 4 limbs 478 -> 322 us.  These kernels and
 // the refresh's run on the latency plan at every count: their loads and Barrett
 // products beside the butterflies gain more from twice the waves a SIMD than
-// the butterflies lose to a fourth group (the 768-ciphertext refresh at 2^14 325
-// -> 313 us, 32 ciphertexts 39 -> 35 us).  The refresh, up to N = 2^15, is two transform kernels
-// (decrypt + inverse, lift + forward + combine), or up to 2^13 for decode-size
-// counts one fused kernel split by output limb; at 2^16 the staged passes of
-// decryption and encryption around the lift.
+// the butterflies lose to a fourth group.  On the other plan : on this one, us, 4
+// limbs, encrypt / decrypt / refresh: 16 of 2^13 9.5 : 9.1 / 8.8 : 8.1 / fused, 200
+// of 2^13 27.2 : 24.9 / 27.0 : 25.2 / 51.7 : 49.0, 768 of 2^13 106 : 95 / 84 : 75 /
+// 160 : 150, 16 of 2^14 15.1 : 14.4 / 15.1 : 13.2 / 36.2 : 32.8, 768 of 2^14 203 :
+// 198 / 184 : 161 / 328 : 314 (the two plans are one at the other sizes).  The
+// refresh, up to N = 2^15, is two transform kernels (decrypt + inverse, lift +
+// forward + combine), or up to 2^13 for decode-size counts one fused kernel split
+// by output limb; at 2^16 the staged passes of decryption and encryption around
+// the lift.
 #include <type_traits>
 
 #include "ntt_core.hpp"
