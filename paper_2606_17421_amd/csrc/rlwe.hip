@@ -62,12 +62,17 @@ __device__ __forceinline__ uint32_t shoup_const(uint32_t w, uint32_t q, double q
   return ws;
 }
 
+// e mod q for |e| < q.
+__device__ __forceinline__ uint32_t small_residue(int32_t e, uint32_t q) {
+  return e < 0 ? static_cast<uint32_t>(e) + q : static_cast<uint32_t>(e);
+}
+
 // (x0 + q0 k - [neg] q0 q1 + e) mod q_l, the refreshed residue of one
 // coefficient: x0 < q0 and k < q1 are the CRT digits, neg the centring flag,
-// e in [-19, 19] the fresh error.  With ka = k + [neg](2 q - q1) (< 2^32; 2 q >
+// |e| < q_l the fresh error.  With ka = k + [neg](2 q - q1) (< 2^32; 2 q >
 // q1) the centring folds into the product q0 ka = q0 k - [neg] q0 q1 (mod q);
-// the lazy Shoup product lies in [0, 2q), so x0 mod q + product + e + q lies
-// in [q - 19, 4q + 19) < 2^32 and three conditional subtractions finish.
+// the lazy Shoup product lies in [0, 2q), so x0 mod q + product + e mod q lies
+// in [0, 4q) < 2^32 and two conditional subtractions finish.
 struct LiftConst {
   uint32_t q, q0l, q0ls, d2;
 };
@@ -83,9 +88,8 @@ __device__ __forceinline__ uint32_t lift_residue(const LiftConst& c, uint32_t x0
   const uint32_t ka = neg ? k + c.d2 : k;
   const uint32_t p = mul_shoup_lazy(ka, c.q0l, c.q0ls, c.q);
   const uint32_t x0l = min(x0, x0 - c.q);
-  uint32_t t = x0l + p + static_cast<uint32_t>(e + static_cast<int32_t>(c.q));
+  uint32_t t = x0l + p + small_residue(e, c.q);
   t = min(t, t - 2 * c.q);
-  t = min(t, t - c.q);
   return min(t, t - c.q);
 }
 
@@ -325,11 +329,6 @@ __global__ __launch_bounds__((WholePlan<LOGN, true>::P::T), (WholePlan<LOGN, tru
       if (l >= 2) __builtin_amdgcn_raw_buffer_store_b32(ax, ro1, vofs, (j0 + i) << 8, 0);
     }
   }
-}
-
-// e mod q for |e| < q.
-__device__ __forceinline__ uint32_t small_residue(int32_t e, uint32_t q) {
-  return e < 0 ? static_cast<uint32_t>(e) + q : static_cast<uint32_t>(e);
 }
 
 // Elements of one row in the coalesced layout, as buffer loads in batches of kB,

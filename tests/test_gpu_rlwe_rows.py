@@ -1,11 +1,12 @@
 """Encryption and decryption below and above one row per CU, with one limb, at the largest
 whole-row ring and in the staged 2^16 form, each with and without a plaintext, against the
-oracle bit for bit."""
+oracle bit for bit; the refresh at the ends of the error range."""
 import numpy as np
 import pytest
 
 from oracle import rlwe as OR
 from test_gpu_rlwe import setup, residues_of
+from workloads import gen
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +36,19 @@ def test_rows_match_the_oracle(gpu_lib, log_n, limbs, count, with_pt):
     ck.ckks_decrypt(ctx, ct, s_ntt, count, limbs, out)
     # an encryption of m with error e decrypts to m + e in every limb
     assert np.array_equal(ck.to_host_u32(out), residues_of(m + e, qs))
+
+
+@pytest.mark.parametrize("log_n,limbs,count", [(10, 3, 2), (13, 2, 2), (13, 4, 65), (14, 3, 2), (15, 2, 1), (16, 2, 1)])
+def test_refresh_with_errors_up_to_the_prime(gpu_lib, log_n, limbs, count):
+    """|e| < q_l in every limb, the extremes on coefficients of every size: residues of a
+    uniform ciphertext, in the fused, two-kernel and staged forms."""
+    ck = gpu_lib
+    ctx, qs, psis, n, st, s, s_ntt, m, e, a = setup(ck, log_n, limbs, count, 950 + log_n)
+    ct = gen.uniform_residues(st["residues"], (count, 2), qs, n)
+    top = min(qs) - 1
+    e[:, ::3], e[:, 1::3] = top, -top
+    out = ck.empty_u32((count, 2, limbs, n))
+    ck.ckks_refresh(ctx, ck.to_device(ct), limbs, s_ntt, ck.to_device(a), ck.to_device(e), count, limbs, out)
+    pick = sorted({0, count - 1})
+    want = OR.refresh(ct[pick].astype(np.uint64), s, a[pick], e[pick], qs, psis, log_n, limbs).astype(np.uint32)
+    assert np.array_equal(ck.to_host_u32(out)[pick], want)
