@@ -29,7 +29,8 @@ Measurement helpers (run under rocprofv3, then summarised into profiles/):
                                               # FETCH_SIZE / WRITE_SIZE runs -> markdown
 
 `roofline.traffic` is read from profiles/<kernel>_<workload>_traffic.md
-(mac_mfma_<cN> for the scalar step, mac_poly_bsgs_d1024_n13 for the BSGS product)
+(mac_mfma_<cN> or rns_mac_<cN> for the scalar step, by the kernels that ran,
+mac_poly_bsgs_d1024_n13 for the BSGS product)
 when that summary was taken on the current kernel source (SHA-256 match);
 otherwise it is null.
 """
@@ -63,6 +64,8 @@ BUTTERFLY_OPS_INV = 9            # per inverse (Gentleman-Sande) butterfly: 3 mu
 _CPU = {}                        # inputs shared with forked oracle workers
 MAC_SOURCE = os.path.join(ROOT, "paper_2606_17421_amd", "csrc", "mac_mfma.hip")
 POLY_SOURCE = os.path.join(ROOT, "paper_2606_17421_amd", "csrc", "mac_valu.hip")
+RNS_SOURCE = os.path.join(ROOT, "paper_2606_17421_amd", "csrc", "mac_rns.hip")
+CHANNELS_TAKEN = 0x524E5301       # the scalar MAC's decision word when the residue channels computed the call
 COPY_WORDS = 64 << 20            # calibration copy: 256 MiB read + 256 MiB written per launch
 COPY_LAUNCHES = 5
 
@@ -140,8 +143,9 @@ def _short(name):
     return re.sub(r"\(.*$", "", name).strip()     # drop the argument list
 
 
-def _counter_means(d, counter):
-    """Mean per-dispatch value of `counter` by short kernel name from a rocprofv3 CSV directory."""
+def _counter_sums(d, counter):
+    """(sum over its dispatches, dispatches) of `counter` by short kernel name from a rocprofv3 CSV
+    directory."""
     f = glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True)
     assert f, f"no counter_collection.csv under {d}"
     acc = {}
@@ -149,7 +153,7 @@ def _counter_means(d, counter):
         if r["Counter_Name"] != counter:
             continue
         acc.setdefault(_short(r["Kernel_Name"]), []).append(float(r["Counter_Value"]))
-    return {k: sum(v) / len(v) for k, v in acc.items()}
+    return {k: (sum(v), len(v)) for k, v in acc.items()}
 
 
 def summarize_trace(d):
@@ -163,27 +167,29 @@ def summarize_trace(d):
               f"{float(r['MinNs']) / 1e3:.1f} | {float(r['MaxNs']) / 1e3:.1f} | {float(r['Percentage']):.1f}% |")
 
 
-def summarize_traffic(d, kernels=("mfma_prep_kernel", "mac_cs_kernel"), source=MAC_SOURCE):
+def summarize_traffic(d, kernels, source=MAC_SOURCE):
     """d holds four rocprofv3 --pmc runs: fetch/ and write/ of the bench command,
     copy_fetch/ and copy_write/ of --copy-calibration.  Traffic is summed over the
-    given kernels (by default the two one ckks_linear_mac_scalar call launches)."""
-    cf = _counter_means(os.path.join(d, "copy_fetch"), "FETCH_SIZE")
-    cw = _counter_means(os.path.join(d, "copy_write"), "WRITE_SIZE")
+    given kernels of one call, the first of which the call launches once."""
+    cf = {k: s / m for k, (s, m) in _counter_sums(os.path.join(d, "copy_fetch"), "FETCH_SIZE").items()}
+    cw = {k: s / m for k, (s, m) in _counter_sums(os.path.join(d, "copy_write"), "WRITE_SIZE").items()}
     ck = [k for k in cf if "neg" in k.lower()]
     assert len(ck) == 1, f"cannot pick the copy kernel among {list(cf)}"
     f_factor = COPY_WORDS * 4 / (cf[ck[0]] * 1024)
     w_factor = COPY_WORDS * 4 / (cw[ck[0]] * 1024)
-    kf = _counter_means(os.path.join(d, "fetch"), "FETCH_SIZE")
-    kw = _counter_means(os.path.join(d, "write"), "WRITE_SIZE")
+    kf = _counter_sums(os.path.join(d, "fetch"), "FETCH_SIZE")
+    kw = _counter_sums(os.path.join(d, "write"), "WRITE_SIZE")
     print(f"- copy kernel `{ck[0]}`: FETCH_SIZE {cf[ck[0]]:.0f} KiB, WRITE_SIZE {cw[ck[0]]:.0f} KiB per launch "
           f"for {COPY_WORDS * 4} bytes each way -> factors {f_factor:.4f} (fetch), {w_factor:.4f} (write)")
     fetch = write = 0.0
     for kname in kernels:
-        names = [k for k in kf if k == kname]
-        assert len(names) == 1, f"cannot pick {kname} among {list(kf)}"
-        fetch += kf[kname] * 1024 * f_factor
-        write += kw[kname] * 1024 * w_factor
-        print(f"- `{kname}`: FETCH_SIZE {kf[kname]:.0f} KiB, WRITE_SIZE {kw[kname]:.0f} KiB per launch")
+        assert kname in kf, f"cannot pick {kname} among {list(kf)}"
+        f_kib, w_kib = kf[kname][0] / kf[kernels[0]][1], kw[kname][0] / kw[kernels[0]][1]
+        fetch += f_kib * 1024 * f_factor
+        write += w_kib * 1024 * w_factor
+        launches = kf[kname][1] / kf[kernels[0]][1]
+        print(f"- `{kname}`: FETCH_SIZE {f_kib:.0f} KiB, WRITE_SIZE {w_kib:.0f} KiB per "
+              + ("launch" if launches == 1 else f"call ({launches:.0f} launches)"))
     print(f"- fetch_bytes_per_launch: {fetch:.6g}")
     print(f"- write_bytes_per_launch: {write:.6g}")
     print(f"- traffic_bytes_per_launch: {fetch + write:.6g}")
@@ -464,10 +470,10 @@ def bench_dte(args):
     bf = bf_inv + bf_fwd
     ms_per_step = wall / args.steps * 1e3
     achieved = (bf_inv * BUTTERFLY_OPS_INV + bf_fwd * BUTTERFLY_OPS_FWD) / (call * 1e-3)
-    # row transfers per ciphertext by the call's passes: decrypt reads 4 and writes 2 scratch rows,
-    # the 2 inverse transforms read and write 2, the lift reads 2 + the error row and writes L_out,
-    # the forward transforms read and write L_out, the combine reads 2 L_out and writes 2 L_out
-    moved = count * n * 4 * (13 + 7 * L_out)
+    # row transfers per ciphertext by the call's two kernels: the first reads c0 and c1 of 2 limbs and
+    # writes 2 scratch rows; the second reads these and the error row, L_out rows of a, and writes c0 and
+    # all but 2 rows of c1, which a copy fills from a
+    moved = count * n * 4 * (11 + 3 * L_out)
     return {
         "metric": "ciphertexts refreshed/s (decrypt-then-encrypt, section 3.2)", "value": count / (ms_per_step * 1e-3),
         "unit": "ciphertexts/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -478,7 +484,7 @@ def bench_dte(args):
                    "log_n": cfg.log_n, "limbs_in": L_in, "limbs_out": L_out, "count": count},
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK / 1e12, "unit": "TOP/s",
                      "frac": achieved / VALU_PEAK, "traffic": None,
-                     "kernel": "ckks_refresh call (pointwise passes + 2 inverse and 4 forward transforms)",
+                     "kernel": "ckks_refresh call (decrypt + inverse transform, lift + forward transform + combine)",
                      "work_per_launch": f"{bf_inv:.4g} inverse butterflies x {BUTTERFLY_OPS_INV} + {bf_fwd:.4g} "
                                         f"forward x {BUTTERFLY_OPS_FWD} lane-ops"},
         "breakdown_ms": {"refresh": call},
@@ -951,7 +957,7 @@ def main():
     ap.add_argument("--copy-calibration", action="store_true")
     ap.add_argument("--summarize-trace", metavar="DIR")
     ap.add_argument("--summarize-traffic", metavar="DIR")
-    ap.add_argument("--traffic-kernels", default="mfma_prep_kernel,mac_cs_kernel",
+    ap.add_argument("--traffic-kernels", default="mfma_prep_kernel<false>,mac_cs_kernel<false>",
                     help="comma-separated kernel names summed by --summarize-traffic")
     ap.add_argument("--traffic-source", default="mac_mfma.hip",
                     help="source file (under the package's csrc/) whose SHA-256 the summary records")
@@ -959,7 +965,7 @@ def main():
     if args.summarize_trace:
         return summarize_trace(args.summarize_trace)
     if args.summarize_traffic:
-        return summarize_traffic(args.summarize_traffic, tuple(args.traffic_kernels.split(",")),
+        return summarize_traffic(args.summarize_traffic, tuple(re.split(r",(?![^<]*>)", args.traffic_kernels)),
                                  os.path.join(ROOT, "paper_2606_17421_amd", "csrc", args.traffic_source))
     if args.gpus != 1:
         print(f"bench.py measures one GPU only (the layer is not sharded across GPUs); got --gpus {args.gpus}",
@@ -1041,12 +1047,14 @@ def main():
     wdig = 3  # weight digits used by the MAC kernel for |round(w*scale)| <= 0x7f7f7f
     if np.max(np.abs(np.rint(W * cfg.scale))) > 0x7F7F7F:
         wdig = 4
-    # four-digit weights of a large layer (2^40 products and more) go through eight int8
-    # residue channels instead of 4 x 4 digit products
-    channels = wdig == 4 and cfg.d_in <= 1024 and macs >= 1 << 40
+    # Large layers of wide weights may have gone through eight int8 residue channels instead of digit
+    # products: the calls leave their decision word in the workspace, behind the digit fragments.
+    word = L * (-(-cfg.d_out // 128) * 8) * -(-cfg.d_in // 64) * 4096 // 4
+    channels = word < ws_mac.numel() and int(ck.to_host_u32(ws_mac[word:word + 1].clone())[0]) == CHANNELS_TAKEN
     ops_per_mac = 16 if channels else 2 * wdig * 4
     achieved = macs * ops_per_mac / (mac_ms * 1e-3)
-    traffic = None if channels else traffic_from_profile(f"mac_mfma_{cfg.key}")
+    traffic = (traffic_from_profile(f"rns_mac_{cfg.key}", RNS_SOURCE) if channels
+               else traffic_from_profile(f"mac_mfma_{cfg.key}"))
     out = {
         "metric": METRIC,
         "value": macs / (ms_per_step * 1e-3),
