@@ -386,7 +386,7 @@ def bench_poly(args):
         "roofline": {"bound": "hbm", "achieved": mac_bytes / (macm * 1e-3) / 1e9, "peak": HBM_PEAK / 1e9,
                      "unit": "GB/s", "frac": mac_bytes / (macm * 1e-3) / HBM_PEAK,
                      "traffic": traffic_from_profile("mac_poly_c5", POLY_SOURCE),
-                     "kernel": "mac_poly_kernel<4>",
+                     "kernel": "mac_poly_kernel<4, true>",
                      "work_per_launch": f"{mac_bytes:.4g} bytes (plaintexts streamed once + ciphertexts)"},
         "breakdown_ms": {"encode_poly": enc, "mac_poly": macm, "rescale": resm},
         "encode_weights_per_s": d * d / (enc * 1e-3),
@@ -796,7 +796,7 @@ def bench_bsgs(args):
         "roofline": {"bound": "hbm", "achieved": mac_bytes / (mac_ms * 1e-3) / 1e9, "peak": HBM_PEAK / 1e9,
                      "unit": "GB/s", "frac": mac_bytes / (mac_ms * 1e-3) / HBM_PEAK,
                      "traffic": traffic_from_profile("mac_poly_bsgs_d1024_n13", POLY_SOURCE),
-                     "kernel": f"mac_poly_kernel<2>: the call's {n2} x {n1} inner-sum MAC, timed alone",
+                     "kernel": f"mac_poly_kernel<2, false>: the call's {n2} x {n1} inner-sum MAC, timed alone",
                      "work_per_launch": f"{mac_bytes:.4g} bytes (plaintexts {pt_bytes:.3g} read once, "
                                         f"{n1} inputs and {n2} outputs)", "launch_ms": mac_ms},
         "call_hbm": {"bytes": pt_bytes + key_bytes, "frac": (pt_bytes + key_bytes) / (head["event_ms"] * 1e-3) / HBM_PEAK,
